@@ -74,31 +74,56 @@ struct GemmArgs {
     const float* pos;    // Patch: position table [N, D]
     int P, N;            // Patch: patches and tokens per frame (Restore: N)
     int G;               // Restore: group size
-    int cus;             // compute units of the device (0: no split of the last round)
-    // set by the launcher: the blocks below head_grid (persistent, at most one per slot) run
-    // large tiles over the rows [0, head), the others small tiles over [head, M),
-    // head = gemm_head_rows(M, Nout, BM, BN, slots);
-    // slots = 0: one tiling for all rows
-    int slots, head_grid;
-    bool mid_tail;       // a partial round of a quarter to half of the grid goes to 128 x 128 tiles
+    int cus;             // compute units of the device (0: unknown)
+    // set by the launcher: division by the grid and by the large tile columns
+    uint32_t div_grid, div_tn;
 };
 
-// Rows that large tiles take when the M rows are split between large tiles (hbm x hbn, `slots`
-// resident blocks) and small ones: the tile rows that fill whole rounds of the large-tile grid.
-// *kind: 1 for a remainder of at most a quarter of a round (64 x 64 tiles), 2 for at most half
-// a round when `mid` (128 x 128 tiles), 0 when every row stays in large tiles (no remainder, or
-// a larger one).  Each output is the same dot product in the same k order in any tiling, so the
-// split does not change results.
-__host__ __device__ inline int gemm_head_rows(int M, int Nout, int hbm, int hbn, int slots,
-                                              int* kind = nullptr, bool mid = false) {
+// n / d for n < 2^24, d < 2^8 or so (n * d < 2^32) by one multiplication with div_magic(d): a
+// kernel's few divisions by values known at launch, which the hardware would do in dozens of
+// instructions each.  div_magic(1) = 0 stands for 2^32.
+inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); }
+__host__ __device__ inline int div_by(int n, uint32_t magic) {
+    return magic ? (int)(((uint64_t)(uint32_t)n * magic) >> 32) : n;
+}
+
+// How the M rows of a bf16 GEMM are cut: large tiles (256 x hbn) over the rows [0, head) -- the
+// tile rows that fill whole rounds of `slots` workgroups -- and one smaller tile shape over
+// [head, M), the rows of the last, partial round.  Each output is the same dot product in the same
+// k order in any tile, so the plan does not change results.
+// The partial round takes the shape with the least rounds x time per tile.  Times per tile,
+// relative to a 256 x 256 tile, measured at K = 1024 and 4096 alike (per-launch overhead taken off,
+// one tile per compute unit: FC2 of width 1024, us: 70 / 41 / 28 / 19.5 / 16.5 for 256 x 256,
+// 128 x 256, 128 x 128, 64 x 128, 64 x 64): the smaller the tile, the more of it is the latency of
+// its loads, barriers and epilogue.
+enum GemmTail : int { TAIL_NONE = 0, TAIL_128x256, TAIL_128x128, TAIL_64x128, TAIL_64x64 };
+struct GemmPlan {
+    int head;
+    int tail;
+};
+__host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slots,
+                                              uint32_t div_slots, uint32_t div_tn) {
     const int tn = Nout / hbn;
-    const int mt = (M + hbm - 1) / hbm;
-    const int mA = (mt * tn / slots) * slots / tn;   // whole tile rows inside the full rounds
-    const int rem = (mt - mA) * tn;                  // large tiles of the partial round
-    int k = 0;
-    if (mA < mt) k = rem * 4 <= slots ? 1 : (mid && rem * 2 <= slots) ? 2 : 0;
-    if (kind) *kind = k;
-    return k ? mA * hbm : M;
+    const int mt = (M + 255) / 256;
+    const int mA = div_by(div_by(mt * tn, div_slots) * slots, div_tn);   // whole tile rows inside the full rounds
+    GemmPlan p = {M, TAIL_NONE};
+    if (mA >= mt) return p;
+    const int rows = M - mA * 256;
+    int best = hbn == 256 ? 100 : 59;                // the partial round in large tiles
+    auto consider = [&](int kind, int bm, int bn, int cost) {
+        const int tiles = (rows + bm - 1) / bm * (Nout / bn);
+        const int c = div_by(tiles + slots - 1, div_slots) * cost;
+        if (c < best) {
+            best = c;
+            p.head = mA * 256;
+            p.tail = kind;
+        }
+    };
+    if (hbn == 256) consider(TAIL_128x256, 128, 256, 59);
+    consider(TAIL_128x128, 128, 128, 39);
+    consider(TAIL_64x128, 64, 128, 27);
+    consider(TAIL_64x64, 64, 64, 23);
+    return p;
 }
 
 void launch_gemm(Epi e, bool bf16, const GemmArgs& a, hipStream_t s);

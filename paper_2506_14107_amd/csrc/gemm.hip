@@ -4,26 +4,30 @@
 // largest possible M and blocks past the live tiles return at once.
 //
 // bf16 path: MFMA v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
-//   * Block tile BM x BN, 4 wavefronts in 2 x 2, each owning (BM/2) x (BN/2) of 32 x 32 tiles.
-//   * k-slices of BK travel global -> LDS with buffer_load_dwordx4 ... lds (no staging registers)
-//     through a ring of S stages: S-1 slices are in flight while one is consumed.  One
-//     wavefront instruction writes 1 KiB of LDS (lane i at base + 16 i).  LDS rows are BK*2
-//     bytes without padding; lane i fetches the global chunk that belongs at its slot: chunk
-//     c of tile row r sits at slot c ^ swz(r), so 16 lanes reading one chunk of 16 rows hit
-//     distinct banks.
+//   * One workgroup of eight wavefronts per compute unit walks block tiles BM x BN; the wavefronts
+//     share a tile WGM x WGN, each owning (BM/WGM) x (BN/WGN) of 32 x 32 tiles.
+//   * Whole rounds of the grid take 256 x 256 tiles (256 x 128 where Nout is no multiple of 256);
+//     the rows left over take the tile shape that finishes them soonest (gemm_plan).
+//   * k-slices of 64 travel global -> LDS with buffer_load_dwordx4 ... lds (no staging registers)
+//     through a ring of S stages.  One wavefront instruction writes 1 KiB of LDS (lane i at
+//     base + 16 i).  LDS rows are 128 bytes without padding; lane i fetches the global chunk that
+//     belongs at its slot: chunk c of tile row r sits at slot c ^ swz(r), so 16 lanes reading one
+//     chunk of 16 rows hit distinct banks.
 //   * Both operands are K-contiguous rows, so A and B fragments are the same 16-byte LDS read:
 //     lane l takes row l%32 and k-slice (l/32)*8 .. +8.  The weight fragment is the MFMA's
 //     first operand, so the accumulator is the transposed tile: lane l, register j holds output
 //     column (j/4)*8 + (l/32)*4 + j%4 of token row l%32 -- four consecutive columns per
 //     register group, stored as one vector by the epilogue.
-//   * The fragments of k-step ks+1 are read while the MFMAs of k-step ks run.
+//   * The fragments of k-step ks+1 are read while the MFMAs of k-step ks run; the smallest tiles
+//     read a whole slice ahead (one MFMA per k-step does not cover an LDS read).
 //   * Tile order: the live tiles (ceil(M/BM) * Nout/BN) go round-robin over the 8 XCDs in
 //     contiguous chunks, each chunk walking groups of 8 tile-rows across all tile-columns, so
 //     an XCD's L2 sees few distinct A and W tiles.
+//   * Every output is one chain of MFMAs in k order from its bias, whatever tile takes it, so a
+//     row's result does not depend on how many other rows the launch has.
 //
 // fp32 path: a plain LDS-tiled VALU GEMM (small fp32 models).
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "dv_internal.h"
@@ -246,21 +250,34 @@ __device__ __forceinline__ void tile_coords(int bid, int mt, int tilesN, int& tm
     const int first_m = group * GM;
     const int gsize = min(mt - first_m, GM);
     const int w_in = lid - group * GM * tilesN;
-    tm = first_m + w_in % gsize;
-    tn = w_in / gsize;
+    tn = gsize == GM ? w_in / GM : w_in / gsize;   // all groups but the last: a shift
+    tm = first_m + w_in - tn * gsize;
+}
+
+// f(R), f(R - 1), ..., f(1) with compile-time arguments
+template <int R, class F>
+__device__ __forceinline__ void drain(F f) {
+    if constexpr (R > 0) {
+        f(std::integral_constant<int, R>());
+        drain<R - 1>(f);
+    }
 }
 
 // ---------------- bf16 MFMA GEMM, pipelined ----------------------------------------------------
-// One block tile of a wave group: the DMA ring keeps S-1 k-slices in flight and the MFMA
-// fragments are always one k-step ahead, across stage boundaries too.  The barrier of stage
-// kt+1 sits just before the first fragment loads of stage kt+1; the DMA of a new stage is issued
-// right after it, into the slot every wave finished reading before that barrier.  The tile is
-// number `bid` of the rows [m0, M); `sm` is the group's LDS and `wave` its index in the group.
-// Every wavefront of the workgroup passes the same barriers (a group without a tile has left).
+// One block tile: the DMA ring keeps S-1 k-slices in flight and the MFMA fragments are always one
+// k-step ahead, across stage boundaries too.  The barrier of stage kt+1 sits just before the first
+// fragment loads of stage kt+1; the DMA of a new stage is issued right after it, into the slot
+// every wave finished reading before that barrier.  The tile is number `bid` of the rows [m0, M);
+// `sm` is the workgroup's LDS.  Every wavefront of the workgroup passes the same barriers.
+// AHEAD (tiles whose wavefronts have one MFMA per k-step): the fragments of a whole slice are read
+// one slice ahead, so a slice costs one barrier and one LDS latency instead of one per k-step, and
+// S slices are in flight.
 // PERSIST: the block goes on to tiles bid + stride, bid + 2 stride, ... of the same rows; when a
 // tile's last k-slice starts, the next tile's first slice and bias are copied into the ring slot
-// that is then free, and the epilogue's slabs sit past that slot.
-template <Epi E, int BM, int BN, int BKD, int S, int WGM, int WGN, bool PERSIST = false>
+// that is then free (an even number of slices; else between the tiles), and the epilogue's slabs
+// sit past that slot.
+template <Epi E, int BM, int BN, int BKD, int S, int WGM, int WGN, bool PERSIST = false,
+          bool AHEAD = false>
 __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int bid, int m0, int M,
                                           int wave, int stride = 0) {
     constexpr int NW = WGM * WGN;                 // wavefronts, WGM x WGN over the block tile
@@ -315,15 +332,15 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
         uint16_t* st = sm + (kt % S) * STAGE;
         const int soff = kt * BKD * 2;
 #pragma unroll
-        for (int t = 0; t < LA; ++t)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA,
-                (__attribute__((address_space(3))) void*)(st + (wave * LA + t) * RPI * BKD), 16,
-                (int)goffA[t], soff, 0, 0);
-#pragma unroll
         for (int t = 0; t < LB; ++t)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rW,
                 (__attribute__((address_space(3))) void*)(st + BM * BKD + (wave * LB + t) * RPI * BKD), 16,
                 (int)goffB[t], soff, 0, 0);
+#pragma unroll
+        for (int t = 0; t < LA; ++t)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA,
+                (__attribute__((address_space(3))) void*)(st + (wave * LA + t) * RPI * BKD), 16,
+                (int)goffA[t], soff, 0, 0);
     };
     // persistent tiles: the tile's bias (BN floats) goes to LDS past the slabs with the DMA of its
     // first slice, so that setting the accumulators waits on no vector memory operation (a
@@ -357,19 +374,31 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
     auto frag = [&](int kt, int ks, bf16x8 (&xa)[TI], bf16x8 (&xb)[TJ]) {
         const uint16_t* st = sm + (kt % S) * STAGE;
         const int c = ks * 2 + hl;
+        // in the order the products need them (B0, A0, B1, ...)
 #pragma unroll
-        for (int i = 0; i < TI; ++i) xa[i] = *(const bf16x8*)(st + offA[i] + (c ^ swA[i]) * 8);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) xb[j] = *(const bf16x8*)(st + offB[j] + (c ^ swB[j]) * 8);
+        for (int q = 0; q < TI + TJ; ++q) {
+            const int n = q < 2 * TJ ? q / 2 : q - TJ;
+            if (q < 2 * TJ && q % 2 == 0) xb[n] = *(const bf16x8*)(st + offB[n] + (c ^ swB[n]) * 8);
+            else if (n < TI) xa[n] = *(const bf16x8*)(st + offA[n] + (c ^ swA[n]) * 8);
+        }
     };
 
     f32x16 acc[TI][TJ];
     const int nk = K / BKD;
+    f32x4 bias_r[TJ][4];   // one tile per call: the bias is requested ahead of the ring
+    if constexpr (!PERSIST) {
 #pragma unroll
-    for (int p = 0; p < S - 1; ++p)
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                bias_r[j][g] = *(const f32x4*)(a.bias + tn * BN + wn * WN + j * 32 + g * 8 + hl * 4);
+    }
+#pragma unroll
+    for (int p = 0; p < (AHEAD ? S : S - 1); ++p)
         if (p < nk) issue(p);
     issue_bias(tn);
-    wait_vm<0>();
+    if (PERSIST || nk < (AHEAD ? S : S - 1)) wait_vm<0>();
+    else wait_vm<(AHEAD ? S - 1 : S - 2) * L>();   // the first slice has landed
     bare_barrier();
     bf16x8 fa[2][TI], fb[2][TJ];
     // one k-slice: MFMAs on the fragments in hand while the next fragments are read.  NEXT:
@@ -436,8 +465,9 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int bc = wn * WN + j * 32 + g * 8 + hl * 4;
-                const f32x4 v = PERSIST ? *(const f32x4*)(bias_lds + bc)
-                                        : *(const f32x4*)(a.bias + tn * BN + bc);
+                f32x4 v;
+                if constexpr (PERSIST) v = *(const f32x4*)(bias_lds + bc);
+                else v = bias_r[j][g];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) b[g * 4 + e] = v[e];
             }
@@ -445,32 +475,101 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
             for (int i = 0; i < TI; ++i) acc[i][j] = b;
         }
 
-        frag(0, 0, fa[0], fb[0]);
         int kt = 0;
-        for (; kt + S - 1 < nk; ++kt) {   // steady state: a new slice enters the ring every step
-            issue(kt + S - 1);            // slot of slice kt-1: every wave read it before a barrier
-            slice(kt, T_(), std::integral_constant<int, (S - 2) * L>());
+        if constexpr (AHEAD) {
+            bf16x8 ga[2][KS][TI], gb[2][KS][TJ];
+            auto read_slice = [&](int k, bf16x8 (&xa)[KS][TI], bf16x8 (&xb)[KS][TJ]) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) frag(k, ks, xa[ks], xb[ks]);
+            };
+            auto mul_slice = [&](const bf16x8 (&xa)[KS][TI], const bf16x8 (&xb)[KS][TJ]) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int q = 0; q < TI * TJ; ++q) {
+                        const int i = q / TJ, j = q % TJ;
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xb[ks][j], xa[ks][i],
+                                                                            acc[i][j], 0, 0, 0);
+                    }
+            };
+            auto step = [&](int k, auto waitn, auto load, auto par) {
+                constexpr int P = decltype(par)::value;
+                wait_vm<decltype(waitn)::value>();
+                bare_barrier();
+                if constexpr (decltype(load)::value) issue(k + S);
+                read_slice(k + 1, ga[P ^ 1], gb[P ^ 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                mul_slice(ga[P], gb[P]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
+            using W = std::integral_constant<int, (S - 2) * L>;
+            read_slice(0, ga[0], gb[0]);
+            for (; kt + 1 + S < nk; kt += 2) {
+                step(kt, W(), T_(), P0());
+                step(kt + 1, W(), T_(), P1());
+            }
+            if (kt + S < nk) {
+                step(kt, W(), T_(), P0());
+                ++kt;
+            }
+            drain<S - 1>([&](auto r) {
+                constexpr int R = decltype(r)::value;
+                if (nk - 1 - kt >= R) {
+                    using WR = std::integral_constant<int, (R - 1) * L>;
+                    if (kt & 1) step(kt, WR(), F_(), P1());
+                    else step(kt, WR(), F_(), P0());
+                    ++kt;
+                }
+            });
+            if (kt & 1) mul_slice(ga[1], gb[1]);
+            else mul_slice(ga[0], gb[0]);
+        } else {
+            frag(0, 0, fa[0], fb[0]);
+            for (; kt + S - 1 < nk; ++kt) {   // steady state: a new slice enters the ring every step
+                issue(kt + S - 1);            // slot of slice kt-1: every wave read it before a barrier
+                slice(kt, T_(), std::integral_constant<int, (S - 2) * L>());
+            }
+            drain<S - 2>([&](auto r) {        // slices kt + 1 .. nk - 1 are in flight
+                constexpr int R = decltype(r)::value;
+                if (nk - 1 - kt >= R) {
+                    slice(kt, T_(), std::integral_constant<int, (R - 1) * L>());
+                    ++kt;
+                }
+            });
         }
-        for (; kt + 1 < nk; ++kt) slice(kt, T_(), std::integral_constant<int, 0>());   // drain
         // persistent: the block's next tile takes its first slice into slot 0 now -- every wave
         // finished reading slot 0 (slice nk - 2) before the last barrier -- so that it lands while
         // this tile's last slice and epilogue run
         const int nbid = bid + stride;
-        const bool more = PERSIST && S == 2 && nk % 2 == 0 && nbid < active;
+        static_assert(!PERSIST || S == 2, "the slot copied into ahead assumes a 2-stage ring");
+        const bool more = PERSIST && nk % 2 == 0 && nbid < active;
         int ntm = 0, ntn = 0;
         if (more) {
             setup(nbid, ntm, ntn);
             issue(0);
             issue_bias(ntn);
         }
-        slice(kt, F_(), std::integral_constant<int, 0>());   // last slice
+        if constexpr (!AHEAD) slice(kt, F_(), std::integral_constant<int, 0>());   // last slice
 
         __syncthreads();   // every wave is done with the LDS ring
         // (persistent: the slabs sit past slot 0, which holds the next tile's first slice)
         float* const slabs = (float*)(PERSIST ? sm + STAGE : sm);
         epilogue_lds<E, TI, TJ>(a, acc, slabs + wave * (32 * (TJ * 32 + 4)),
                                 m0 + tm * BM + wm * WM, tn * BN + wn * WN, M, lane);
-        if (!more) break;
+        if (!more) {
+            if (!PERSIST || nbid >= active) break;
+            // an odd number of slices: nothing was copied ahead
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            bare_barrier();   // every wave is done with its slab
+            bid = nbid;
+            setup(bid, tm, tn);
+            issue(0);
+            issue_bias(tn);
+            wait_vm<0>();
+            bare_barrier();
+            continue;
+        }
         bid = nbid;
         tm = ntm;
         tn = ntn;
@@ -483,128 +582,79 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
 }
 
 // LDS of one block tile: the DMA ring, reused by the epilogue's per-wave slabs
-template <int BM, int BN, int BKD, int S, int WGM, int WGN>
+template <int BM, int BN, int S, int WGM, int WGN>
 constexpr size_t pipe_lds_bytes() {
-    constexpr size_t ring = (size_t)S * (BM + BN) * BKD * 2;
+    constexpr size_t ring = (size_t)S * (BM + BN) * 64 * 2;
     constexpr size_t slabs = (size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4;
     return ring > slabs ? ring : slabs;
 }
+constexpr size_t PIPE_LDS = 160 * 1024;   // all of a compute unit's LDS: one workgroup per unit
 
-// Tail tiles of a split launch: 64 x 64, 64-deep k-slices in a 4-stage ring (three in flight: a
-// tail tile is bound by the latency of its k-loop, so few barriers and deep prefetch pay; 32-deep
-// slices in 3 or 8 stages measured slower), one per group of four wavefronts.
-constexpr int TBM = 64, TBN = 64, TBK = 64, TS = 4;
-constexpr size_t TAIL_LDS = pipe_lds_bytes<TBM, TBN, TBK, TS, 2, 2>();
-// Middle tail tiles (a partial round of a quarter to half of the grid): 128 x 128, a 2-stage
-// ring of 64-deep slices, one per group of four wavefronts.
-constexpr int MBM = 128, MBN = 128, MBK = 64, MS = 2;
-constexpr size_t MID_LDS = pipe_lds_bytes<MBM, MBN, MBK, MS, 2, 2>();
+// The tiles BM x BN of the rows [m0, M), walked by the grid one at a time.
+template <Epi E, int BM, int BN, int S, int WGM, int WGN, bool AHEAD>
+__device__ __forceinline__ void walk_tiles(const GemmArgs& a, uint16_t* sm, int m0, int M, int wave) {
+    static_assert(pipe_lds_bytes<BM, BN, S, WGM, WGN>() <= PIPE_LDS, "LDS");
+    if (wave >= WGM * WGN) return;
+    const int n = (M - m0 + BM - 1) / BM * (a.Nout / BN);
+    for (int t = blockIdx.x; t < n; t += gridDim.x) {
+        pipe_tile<E, BM, BN, 64, S, WGM, WGN, false, AHEAD>(a, sm, t, m0, M, wave);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        bare_barrier();   // every wave is done with its slab: the next tile's copies may land
+    }
+}
 
-// Block tiles BM x BN of WGM x WGN wavefronts.  With a.slots set, the launch is split: the
-// a.head_grid blocks below it (at most one per slot) are persistent and take the tiles of the
-// rows [0, head) that fill whole rounds of the grid (gemm_head_rows) -- tile bid, bid +
-// head_grid, ... -- each tile's first k-slice and bias arriving during the previous tile's
-// epilogue; the blocks after them cut the remaining rows into 64 x 64 tiles (a partial round of
-// at most a quarter of the grid) or 128 x 128 tiles (at most half, with a.mid_tail), one per
-// group of four wavefronts, so that the last, partial round spreads over many compute units.
-// A tile's outputs are the same whichever block takes it (one k order per output).
-template <Epi E, int BM, int BN, int BKD, int S, int WPE, int WGM, int WGN>
-__global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+// One workgroup per compute unit (the grid), tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the
+// large tiles over the rows [0, head), then of the plan's smaller tiles over [head, M).  BN: width
+// of the large tiles.  The ring depths fill LDS: a small tile is bound by the latency of its loads.
+// Measured against one workgroup per tile, the last round in 64 x 64 tiles up to a quarter of it
+// and 128 x 128 up to half (us, before -> after; widths 1024, K = 4096 for FC2): FC2 at 340 / 700 /
+// 2056 rows 26.1 -> 18.8, 27.0 -> 19.3, 54.2 -> 31.4; QKV at 700 rows 18.6 -> 12.0; out-projection at
+// 2056 19.2 -> 12.9; at 37120 rows FC2 341 -> 312, out-projection 132 -> 125, FC1 305 -> 299.
+template <Epi E, int BN>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_pipe_k(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int NW = WGM * WGN;
-    const int wave = threadIdx.x >> 6;
+    uint16_t* sm = (uint16_t*)smem;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar LDS addresses
     const int M = a.Mdev ? *a.Mdev : a.Mconst;
-    if (!a.slots) {
-        pipe_tile<E, BM, BN, BKD, S, WGM, WGN>(a, (uint16_t*)smem, blockIdx.x, 0, M, wave);
-        return;
+    const GemmPlan p = gemm_plan(M, a.Nout, BN, gridDim.x, a.div_grid, a.div_tn);
+    if (p.head > 0) {
+        if constexpr (BN == 256) {
+            pipe_tile<E, 256, 256, 64, 2, 2, 4, true>(a, sm, blockIdx.x, 0, p.head, wave, gridDim.x);
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            bare_barrier();
+        } else {
+            walk_tiles<E, 256, 128, 3, 4, 2, false>(a, sm, 0, p.head, wave);
+        }
     }
-    int kind = 0;
-    const int head = gemm_head_rows(M, a.Nout, BM, BN, a.slots, &kind, a.mid_tail);
-    if ((int)blockIdx.x < a.head_grid) {
-        pipe_tile<E, BM, BN, BKD, S, WGM, WGN, true>(a, (uint16_t*)smem, blockIdx.x, 0, head, wave,
-                                                     a.head_grid);
-        return;
+    switch (p.tail) {
+        case TAIL_128x256:
+            if constexpr (BN == 256) walk_tiles<E, 128, 256, 3, 2, 4, false>(a, sm, p.head, M, wave);
+            break;
+        case TAIL_128x128: walk_tiles<E, 128, 128, 5, 2, 4, false>(a, sm, p.head, M, wave); break;
+        case TAIL_64x128: walk_tiles<E, 64, 128, 6, 2, 4, true>(a, sm, p.head, M, wave); break;
+        case TAIL_64x64: walk_tiles<E, 64, 64, 9, 2, 2, true>(a, sm, p.head, M, wave); break;
+        default: break;
     }
-    static_assert(NW % 4 == 0, "tail tiles take groups of four wavefronts");
-    const int grp = wave / 4;
-    const int tb = ((int)blockIdx.x - a.head_grid) * (NW / 4) + grp;
-    if (kind == 2)
-        pipe_tile<E, MBM, MBN, MBK, MS, 2, 2>(a, (uint16_t*)(smem + grp * MID_LDS), tb, head, M,
-                                             wave % 4);
-    else
-        pipe_tile<E, TBM, TBN, TBK, TS, 2, 2>(a, (uint16_t*)(smem + grp * TAIL_LDS), tb, head, M,
-                                             wave % 4);
 }
 
-template <Epi E, int BM, int BN, int BKD, int S, int WPE, int WGM, int WGN>
-constexpr size_t pipe_kernel_lds() {
-    constexpr size_t t0 = pipe_lds_bytes<BM, BN, BKD, S, WGM, WGN>();
-    constexpr size_t ring_b = (size_t)S * (BM + BN) * BKD * 2;
-    constexpr size_t slab_end =
-        (size_t)(BM + BN) * BKD * 2 + (size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4;
-    constexpr size_t tp = (ring_b > slab_end ? ring_b : slab_end) + (size_t)BN * 4;
-    constexpr size_t t = t0 > tp ? t0 : tp;
-    constexpr size_t tail = (TAIL_LDS > MID_LDS ? TAIL_LDS : MID_LDS) * (WGM * WGN / 4);
-    return t > tail ? t : tail;
-}
-
-// Blocks of this configuration that fit on one compute unit (0 if the query fails).
-template <Epi E, int BM, int BN, int BKD, int S, int WPE, int WGM, int WGN>
-int pipe_blocks_per_cu(const void* k, size_t lds) {
-    static int n = -1;
-    if (n < 0) {
-        int v = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, WGM * WGN * 64, lds) != hipSuccess)
-            v = 0;
-        n = v;
-    }
-    return n;
-}
-
-// split: cut the last partial round into 64 x 64 tiles (needs a.cus and Nout % 64 == 0)
-template <Epi E, int BM, int BN, int BKD, int S, int WPE, int WGM = 2, int WGN = 2>
-void launch_pipe(const GemmArgs& a0, hipStream_t s, bool split = true) {
+template <Epi E, int BN>
+void launch_pipe(const GemmArgs& a0, hipStream_t s) {
     static bool raised = false;
-    constexpr size_t lds = pipe_kernel_lds<E, BM, BN, BKD, S, WPE, WGM, WGN>();
-    static_assert(lds <= 160 * 1024, "LDS exceeds 160 KiB");
-    auto k = gemm_bf16_pipe_k<E, BM, BN, BKD, S, WPE, WGM, WGN>;
+    auto k = gemm_bf16_pipe_k<E, BN>;
     if (!raised) {
         (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
+                                  (int)PIPE_LDS);
         raised = true;
     }
+    // one block per compute unit, or per smallest tile when there are fewer
+    const int tiles = ((a0.Mmax + 63) / 64) * (a0.Nout / 64);
+    const int grid = std::min(tiles, a0.cus > 0 ? a0.cus : 256);
+    if (grid <= 0) return;
     GemmArgs a = a0;
-    const int tn = a.Nout / BN;
-    a.head_grid = ((a.Mmax + BM - 1) / BM) * tn;
-    a.slots = 0;
-    int grid = a.head_grid;
-    const int per_cu = split && a.cus > 0 && a.Nout % TBN == 0
-                           ? pipe_blocks_per_cu<E, BM, BN, BKD, S, WPE, WGM, WGN>((const void*)k, lds)
-                           : 0;
-    if (per_cu > 0) {
-        a.slots = a.cus * per_cu;
-        // persistent head blocks where tiles can follow one another (a 2-stage ring and an even
-        // number of k-slices: pipe_tile's `more`); their number is a multiple of the 8 XCDs, so
-        // that tile bid + k * head_grid lands on the XCD tile_coords assigns it.  Otherwise one
-        // block per head tile, as each block then takes a single tile.
-        if (S == 2 && (a.K / BKD) % 2 == 0) a.head_grid = std::min(a.head_grid, a.slots);
-        grid = a.head_grid;
-        // 128 x 128 tiles for a partial round of a quarter to half of the grid where the output
-        // has at most four large tile columns (FC2, out-projection): ViT-B/16 (64 frames) FC2
-        // 1.05 -> 0.84 ms, out-projection 0.39 -> 0.33 ms per sweep, ViT-L/14 FC2 -2.4 %;
-        // the wider outputs, whose partial rounds are a smaller share, measured 0.5 % slower
-        a.mid_tail = a.Nout % MBN == 0 && tn <= 4;
-        // the tail holds at most a quarter round of large tiles in 64 x 64 tiles (slots/4/tn
-        // tile rows) or at most half a round in 128 x 128 tiles
-        const int rows64 = std::min(a.Mmax, (a.slots / 4 / tn + 1) * BM);
-        const int tiles64 = ((rows64 + TBM - 1) / TBM) * (a.Nout / TBN);
-        const int rows128 = std::min(a.Mmax, (a.slots / 2 / tn + 1) * BM);
-        const int tiles128 = a.mid_tail ? ((rows128 + MBM - 1) / MBM) * (a.Nout / MBN) : 0;
-        constexpr int per_block = WGM * WGN / 4;
-        grid += (std::max(tiles64, tiles128) + per_block - 1) / per_block;
-    }
-    if (grid > 0) hipLaunchKernelGGL(k, dim3(grid), dim3(WGM * WGN * 64), lds, s, a);
+    a.div_grid = div_magic(grid);
+    a.div_tn = div_magic(a.Nout / BN);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(512), PIPE_LDS, s, a);
 }
 
 // ---------------- fp32 VALU GEMM: block tile 64 x 64, k-step 16, 4 x 4 outputs per thread ---
@@ -658,18 +708,6 @@ __global__ __launch_bounds__(256) void gemm_f32_k(GemmArgs a) {
     }
 }
 
-
-// Tile configuration: 0 the choice in launch_one; tuning overrides (DV_GEMM_CFG): 1 = 256 x 128
-// everywhere, 3 = without the split last round.
-int gemm_cfg() {
-    static int v = -1;
-    if (v < 0) {
-        const char* e = getenv("DV_GEMM_CFG");
-        v = e ? atoi(e) : 0;
-    }
-    return v;
-}
-
 template <Epi E>
 void launch_one(bool bf16, const GemmArgs& a, hipStream_t s) {
     if (!bf16) {
@@ -677,14 +715,8 @@ void launch_one(bool bf16, const GemmArgs& a, hipStream_t s) {
         hipLaunchKernelGGL(gemm_f32_k<E>, dim3(grid), dim3(256), 0, s, a);
         return;
     }
-    // 256 x 256 tiles of eight wavefronts with a double-buffered 64-deep k-slice (one block per
-    // CU) wherever Nout allows, else 256 x 128 tiles, two blocks per CU
-    const bool wide = a.Nout % 256 == 0;
-    const int cfg = gemm_cfg();
-    const bool big = cfg != 1 && wide;
-    const bool split = cfg != 3;
-    if (big) launch_pipe<E, 256, 256, 64, 2, 2, 2, 4>(a, s, split);
-    else launch_pipe<E, 256, 128, 32, 3, 2>(a, s, split);
+    if (a.Nout % 256 == 0) launch_pipe<E, 256>(a, s);
+    else launch_pipe<E, 128>(a, s);
 }
 
 }  // namespace

@@ -1,0 +1,42 @@
+"""The bf16 GEMM's tile plan: every tile shape gives the same bits, at the edges of each shape."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth.configs import ModelConfig
+
+from .gpu_util import check_close, dev, encoder, host, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+# outputs 768 / 256 / 1024 (256-wide large tiles) and 1152 / 384 / 1536 (128-wide for the first
+# two); 50 tokens.  Patch 8 gives the patch GEMM three k-slices (odd), patch 16 twelve.
+WIDE = ModelConfig(112, 16, 1, 256, 4, 1024, "bf16")
+NARROW = ModelConfig(112, 16, 1, 384, 6, 1536, "bf16")
+ODD_K = ModelConfig(56, 8, 1, 256, 4, 512, "bf16")
+
+
+@pytest.mark.parametrize("m", [WIDE, NARROW, ODD_K], ids=["wide", "narrow", "odd-k"])
+def test_tile_plan_bitwise(m):
+    """One frame at a time (50 rows, the smallest tiles) against batches whose row counts take
+    every tile shape, whole rounds of large tiles with and without a remainder among them."""
+    torch = require_gpu()
+    n = 700
+    blob = synth.make_blob(m, 51)
+    base = np.random.default_rng(52).standard_normal((8, 3, m.image_size, m.image_size))
+    gain = np.linspace(0.5, 1.5, n).reshape(n, 1, 1, 1)
+    fr = (base[np.arange(n) % 8] * gain).astype(np.float32)
+    off = float("-inf")
+    big = encoder(m, blob, n)
+    one = encoder(m, blob, 1)
+    want = one.encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
+    torch.cuda.synchronize()
+    for k in (2, 7, 21, 61, 122, 190, 328, 350, 700):
+        got = big.encode(dev(fr[:k]), 1, off, want_masks=False, want_tokens=True)
+        torch.cuda.synchronize()
+        for x, y in ((got[0], want[0]), (got[2], want[2])):
+            assert np.array_equal(host(x), host(y)[:k]), f"{k} frames"
+    ref = oracle.dense_vit(fr[-2:], blob, m.as_dict(), return_tokens=True)
+    check_close(host(got[0])[-2:], ref[0], "bf16", "embeddings")
+    check_close(host(got[2])[-2:], ref[1], "bf16", "tokens")
