@@ -75,7 +75,8 @@ struct GemmArgs {
     int P, N;            // Patch: patches and tokens per frame (Restore: N)
     int G;               // Restore: group size
     int cus;             // compute units of the device (0: unknown)
-    // set by the launcher: division by the grid and by the large tile columns
+    // set by the launcher: division by the grid (fp32: by the compute units) and by the large tile
+    // columns
     uint32_t div_grid, div_tn;
 };
 

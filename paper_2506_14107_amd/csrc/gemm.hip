@@ -26,7 +26,7 @@
 //   * Every output is one chain of MFMAs in k order from its bias, whatever tile takes it, so a
 //     row's result does not depend on how many other rows the launch has.
 //
-// fp32 path: a plain LDS-tiled VALU GEMM (small fp32 models).
+// fp32 path: the same scheme on v_mfma_f32_16x16x4_f32 (f32_tile).
 #include <algorithm>
 #include <type_traits>
 
@@ -69,35 +69,28 @@ __device__ inline u32x2 pack_bf16x4(f32x4 v) {
     return __builtin_bit_cast(u32x2, h);
 }
 
-template <Epi E, bool BF>
-__device__ inline void epi_store(const GemmArgs& a, int row, int col, float acc) {
-    float v = acc + a.bias[col];
+// fp32 path: the sums (bias included) of four consecutive columns of one row to their output
+template <Epi E>
+__device__ inline void epi_store4(const GemmArgs& a, int row, int col, f32x4 v) {
+    auto at = [&](const float* p, size_t r) { return *(const f32x4*)(p + r * a.Nout + col); };
+    size_t o = row;   // output row
     if constexpr (E == Epi::Patch) {
-        const int f = row / a.P, k = row % a.P;
-        const int D = a.Nout;
-        v += a.pos[(size_t)(1 + k) * D + col];
-        ((float*)a.out)[((size_t)f * a.N + 1 + k) * D + col] = v;
-    } else if constexpr (E == Epi::Qkv) {
-        if (BF) ((uint16_t*)a.out)[(size_t)row * a.Nout + col] = f32_to_bf16(v);
-        else ((float*)a.out)[(size_t)row * a.Nout + col] = v;
+        const int f = row / a.P, k = row - f * a.P;
+        v += at(a.pos, 1 + k);
+        o = (size_t)f * a.N + 1 + k;
     } else if constexpr (E == Epi::OProj) {
-        v += a.resid[(size_t)a.idx[row] * a.Nout + col];
-        ((float*)a.out)[(size_t)row * a.Nout + col] = v;
+        v += at(a.resid, a.idx[row]);
     } else if constexpr (E == Epi::Fc1) {
-        v = gelu_erf(v);
-        if (BF) ((uint16_t*)a.out)[(size_t)row * a.Nout + col] = f32_to_bf16(v);
-        else ((float*)a.out)[(size_t)row * a.Nout + col] = v;
+        v = f32x4{gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])};
     } else if constexpr (E == Epi::Fc2) {
-        v += a.resid[(size_t)row * a.Nout + col];
-        ((float*)a.out)[(size_t)a.idx[row] * a.Nout + col] = v;
-    } else if constexpr (E == Epi::Delta) {
-        ((float*)a.out)[(size_t)row * a.Nout + col] = v;
-    } else {  // Restore: a reused token's row from its reference token's new row
+        v += at(a.resid, row);
+        o = a.idx[row];
+    } else if constexpr (E == Epi::Restore) {   // a reused token's row from its reference's new row
         const int t = a.idx[row], f = t / a.N;
-        const int rt = (f / a.G * a.G) * a.N + t % a.N;
-        v += a.resid[(size_t)rt * a.Nout + col];
-        ((float*)a.out)[(size_t)t * a.Nout + col] = v;
+        v += at(a.resid, (size_t)(f / a.G * a.G) * a.N + t % a.N);
+        o = t;
     }
+    *(f32x4*)((float*)a.out + o * a.Nout + col) = v;
 }
 
 __device__ inline void wave_lds_sync() {
@@ -657,62 +650,141 @@ void launch_pipe(const GemmArgs& a0, hipStream_t s) {
     hipLaunchKernelGGL(k, dim3(grid), dim3(512), PIPE_LDS, s, a);
 }
 
-// ---------------- fp32 VALU GEMM: block tile 64 x 64, k-step 16, 4 x 4 outputs per thread ---
-constexpr int FBM = 64, FBN = 64, FBK = 16;
+// ---------------- fp32 MFMA GEMM ---------------------------------------------------------------
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A block of four wavefronts (2 x 2) takes tiles of
+// 32W x 32W, each wavefront W x W tiles of 16 x 16; k-slices of 32 floats go through the same kind of
+// LDS ring as the bf16 path's (128-byte rows, the same swizzle).  Lane l reads 16 bytes of row l%16:
+// k = 16 ks + 4 (l/16) + t for t = 0..3, its operands of four MFMAs, on both sides alike.  The weights
+// are the first operand, so lane l ends with four consecutive columns of token row l%16.  Every
+// output is four chains of MFMAs (one per t) in k order, added at the end, whatever the tile.
+// Bound by the fp32 matrix rate (256 FLOP per clock and compute unit; 64 x 64 tiles need 16 bytes of
+// operands per clock), or, in small models, by latency: 32 x 32 tiles spread few rows over more units.
+// Against 64 x 64 tiles of VALU products (us): FC2 of width 768, about 1200 rows 299 -> 49, FC1 122 ->
+// 41, QKV 127 -> 32; FC2 of width 192, 300 rows 78 -> 9.8.  Distance to 64-bit results halved.
+constexpr size_t F32_LDS = 64 * 1024;   // two blocks per compute unit
+
+template <Epi E, int W, int S>
+__device__ __forceinline__ void f32_tile(const GemmArgs& a, float* sm, int t, int M, int wave) {
+    constexpr int BT = 32 * W, BK = 32, RPI = 8, LR = BT / RPI / 4, L = 2 * LR;
+    constexpr int STAGE = 2 * BT * BK;
+    static_assert((size_t)S * STAGE * 4 <= F32_LDS, "LDS");
+    int tm, tn;
+    tile_coords(t, (M + BT - 1) / BT, a.Nout / BT, tm, tn);
+    const int lane = threadIdx.x & 63, lr = lane & 15, g = lane >> 4;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int K = a.K, nk = K / BK;
+    uint32_t goffA[LR], goffB[LR];
+#pragma unroll
+    for (int u = 0; u < LR; ++u) {
+        const int r = (wave * LR + u) * RPI + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        const int grow = tm * BT + r;
+        const int arow = a.a_idx ? (grow < M ? a.a_idx[grow] : 0) : grow;   // gathered A rows
+        goffA[u] = ((uint32_t)arow * K + c * 4) * 4;
+        goffB[u] = ((uint32_t)(tn * BT + r) * K + c * 4) * 4;
+    }
+    const auto rA = buf_rsrc(a.A, BUF_ANY);
+    const auto rW = buf_rsrc(a.W, BUF_ANY);
+    f32x4 acc[4][W][W];   // a chain per t: independent MFMAs, and shorter sums to round
+    f32x4 bias[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        bias[j] = *(const f32x4*)(a.bias + tn * BT + (wn * W + j) * 16 + g * 4);
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto issue = [&](int kt) {
+        float* st = sm + (kt % S) * STAGE;
+#pragma unroll
+        for (int u = 0; u < LR; ++u) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rW,
+                (__attribute__((address_space(3))) void*)(st + (BT + (wave * LR + u) * RPI) * BK), 16,
+                (int)goffB[u], kt * BK * 4, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA,
+                (__attribute__((address_space(3))) void*)(st + (wave * LR + u) * RPI * BK), 16,
+                (int)goffA[u], kt * BK * 4, 0, 0);
+        }
+    };
+    auto multiply = [&](int kt) {
+        const float* st = sm + (kt % S) * STAGE;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            f32x4 xa[W], xb[W];
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const int ra = (wm * W + i) * 16 + lr, rb = (wn * W + i) * 16 + lr, c = ks * 4 + g;
+                xb[i] = *(const f32x4*)(st + (BT + rb) * BK + (c ^ ((rb >> 1) & 7)) * 4);
+                xa[i] = *(const f32x4*)(st + ra * BK + (c ^ ((ra >> 1) & 7)) * 4);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < W; ++i)
+#pragma unroll
+                    for (int j = 0; j < W; ++j)
+                        acc[e][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xb[j][e], xa[i][e],
+                                                                            acc[e][i][j], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < S - 1; ++p)
+        if (p < nk) issue(p);
+    int kt = 0;
+    for (; kt + S - 1 < nk; ++kt) {
+        wait_vm<(S - 2) * L>();   // slice kt has landed; this wave's reads of slice kt - 1 are done
+        bare_barrier();
+        issue(kt + S - 1);        // into the slot of slice kt - 1
+        multiply(kt);
+    }
+    drain<S - 1>([&](auto r) {    // slices kt .. nk - 1 are in flight
+        constexpr int R = decltype(r)::value;
+        if (nk - kt >= R) {
+            wait_vm<(R - 1) * L>();
+            bare_barrier();
+            multiply(kt);
+            ++kt;
+        }
+    });
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const int row = tm * BT + (wm * W + i) * 16 + lr;
+        if (row >= M) continue;
+#pragma unroll
+        for (int j = 0; j < W; ++j)
+            epi_store4<E>(a, row, tn * BT + (wn * W + j) * 16 + g * 4,
+                          (acc[0][i][j] + acc[1][i][j]) + (acc[2][i][j] + acc[3][i][j]) + bias[j]);
+    }
+}
 
 template <Epi E>
 __global__ __launch_bounds__(256) void gemm_f32_k(GemmArgs a) {
-    __shared__ float sA[FBK][FBM + 4];
-    __shared__ float sB[FBK][FBN + 4];
+    __shared__ __attribute__((aligned(16))) float sm[F32_LDS / 4];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int M = a.Mdev ? *a.Mdev : a.Mconst;
-    const int tilesN = a.Nout / FBN;
-    const int tm = blockIdx.x / tilesN, tn = blockIdx.x % tilesN;
-    if (tm * FBM >= M) return;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int K = a.K;
-    const float* A = (const float*)a.A;
-    const float* W = (const float*)a.W;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += FBK) {
-        // 64 rows x 16 k of A and of W: 1024 values each, 4 per thread
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int e = tid + 256 * t;
-            const int rr = e / FBK, kk = e % FBK;
-            const int grow = tm * FBM + rr;
-            const int arow = a.a_idx ? (grow < M ? a.a_idx[grow] : 0) : grow;
-            sA[kk][rr] = A[(size_t)arow * K + k0 + kk];
-            sB[kk][rr] = W[(size_t)(tn * FBN + rr) * K + k0 + kk];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < FBK; ++kk) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = sA[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = sB[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = tm * FBM + ty * 4 + i;
-        if (row >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) epi_store<E, false>(a, row, tn * FBN + tx * 4 + j, acc[i][j]);
+    // 32 x 32 tiles unless as many 64 x 64 tiles as the compute units take in as short a time: a
+    // quarter of the work each, about a tenth more for operand traffic and barriers
+    const int t64 = (M + 63) / 64 * (a.Nout / 64), t32 = (M + 31) / 32 * (a.Nout / 32);
+    const int r64 = div_by(t64 + a.cus - 1, a.div_grid), r32 = div_by(t32 + a.cus - 1, a.div_grid);
+    const bool large = r64 * 40 <= r32 * 11;
+    const int n = large ? t64 : t32;
+    for (int t = blockIdx.x; t < n; t += gridDim.x) {
+        if (large) f32_tile<E, 2, 4>(a, sm, t, M, wave);
+        else f32_tile<E, 1, 8>(a, sm, t, M, wave);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        bare_barrier();   // every wave has read its last slice: the next tile's copies may land
     }
 }
 
 template <Epi E>
 void launch_one(bool bf16, const GemmArgs& a, hipStream_t s) {
     if (!bf16) {
-        const int grid = ((a.Mmax + FBM - 1) / FBM) * (a.Nout / FBN);
-        hipLaunchKernelGGL(gemm_f32_k<E>, dim3(grid), dim3(256), 0, s, a);
+        GemmArgs f = a;
+        if (f.cus <= 0) f.cus = 256;
+        f.div_grid = div_magic(f.cus);
+        const int grid = std::min(((a.Mmax + 31) / 32) * (a.Nout / 32), 2 * f.cus);
+        if (grid > 0) hipLaunchKernelGGL(gemm_f32_k<E>, dim3(grid), dim3(256), 0, s, f);
         return;
     }
     if (a.Nout % 256 == 0) launch_pipe<E, 256>(a, s);

@@ -40,3 +40,27 @@ def test_tile_plan_bitwise(m):
     ref = oracle.dense_vit(fr[-2:], blob, m.as_dict(), return_tokens=True)
     check_close(host(got[0])[-2:], ref[0], "bf16", "embeddings")
     check_close(host(got[2])[-2:], ref[1], "bf16", "tokens")
+
+
+# fp32: head dims 16 to 128 (one attention variant each), token counts around its 64-key steps and
+# 16-query tiles, widths that are odd multiples of 64; 700 frames take the 64 x 64 GEMM tiles
+@pytest.mark.parametrize("S,p,D,H,n", [
+    (112, 16, 192, 3, 700), (64, 8, 192, 12, 9), (224, 14, 192, 6, 5), (64, 16, 384, 8, 30),
+    (128, 16, 320, 4, 11), (112, 16, 192, 2, 7), (112, 16, 448, 4, 7), (112, 16, 256, 2, 7)])
+def test_fp32_tiles_bitwise(S, p, D, H, n):
+    """One frame at a time (32 x 32 tiles) against the batch bit for bit, and the oracle."""
+    torch = require_gpu()
+    m = ModelConfig(S, p, 1, D, H, 4 * D, "f32")
+    blob = synth.make_blob(m, 53)
+    base = np.random.default_rng(54).standard_normal((8, 3, S, S))
+    gain = np.linspace(0.5, 1.5, n).reshape(n, 1, 1, 1)
+    fr = (base[np.arange(n) % 8] * gain).astype(np.float32)
+    off = float("-inf")
+    got = encoder(m, blob, n).encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
+    one = encoder(m, blob, 1).encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(got[0]), host(one[0]))
+    assert np.array_equal(host(got[2]), host(one[2]))
+    ref = oracle.dense_vit(fr[-2:], blob, m.as_dict(), return_tokens=True)
+    check_close(host(got[0])[-2:], ref[0], "f32", "embeddings")
+    check_close(host(got[2])[-2:], ref[1], "f32", "tokens")
