@@ -409,7 +409,7 @@ __device__ __forceinline__ void store_row(uint16_t* dst, int lane, float l,
 // ---- per-frame items ---------------------------------------------------------------------------
 // Work split: T = ceil(q/32) query tiles over AW wavefronts, each tile over all key blocks.
 template <int DH>
-__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char* smem);
+__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int part, char* smem);
 
 template <int DH>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 4 : 2, DH == 64 ? 4 : 2)))
@@ -432,20 +432,23 @@ void attn_mfma_k(AttnArgs a) {
         for (int e = r; e < U * a.G; e += R) {
             const int u = x + 8 * (e % U), j = e / U;
             const int f = u / a.H * a.G + j;
-            if (u < units && f < a.F) attn_item<DH>(a, f, u % a.H, smem);
+            if (u < units && f < a.F) attn_item<DH>(a, f, u % a.H, 0, smem);
             lds_barrier();   // the next item restages K/V over this item's LDS
         }
     } else {
-        for (int item = blockIdx.x; item < a.F * a.H; item += gridDim.x) {
-            attn_item<DH>(a, item / a.H, item % a.H, smem);
+        const int fh = a.F * a.H;
+        for (int item = blockIdx.x; item < fh * a.parts; item += gridDim.x) {
+            const int part = item / fh, i = item - part * fh;
+            attn_item<DH>(a, i / a.H, i % a.H, part, smem);
             lds_barrier();
         }
     }
 }
 
-// One work item: frame f, head h.  Every thread of the block takes the same path.
+// One work item: frame f, head h, its query tiles part, part + a.parts, ...  Every thread of the
+// block takes the same path.
 template <int DH>
-__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char* smem) {
+__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int part, char* smem) {
     constexpr int KS = DH / 16;          // k-steps of S^T
     constexpr int DB = (DH + 31) / 32;   // 32-row blocks of O^T
     constexpr int CH = DH / 8;           // 16-byte chunks per row
@@ -464,27 +467,41 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char*
     const uint16_t* qkv = (const uint16_t*)a.qkv;
     const int q0 = a.qoff[f], q1 = a.qoff[f + 1];
     const int ntile = (q1 - q0 + 31) / 32;
-    if (ntile <= a.tile_cut) return;   // none, or taken by per-tile wavefronts
+    // none, or taken by per-tile wavefronts, or by the other parts
+    if (ntile <= a.tile_cut || part >= ntile) return;
 
     // stage K and V rows (row-major, 16-byte chunks); keys past N repeat key N-1 (finite data
-    // whose scores are masked).  Up to four chunks per thread are gathered before any store.
+    // whose scores are masked).  Up to SU chunks per thread are gathered before any store
+    // (257 keys of head dim 64 in one pass).
+    constexpr int SU = 5;
     const int total = g.npad * CH;
-    for (int c0 = tid; c0 < total; c0 += 4 * NT) {
-        size_t rowoff[4];
-        u32x4 kv[4], vv[4];
+    // the first tile's queries are requested ahead of the keys
+    auto load_q = [&](int t, bf16x8 (&qf)[KS]) {
+        const int myq = q0 + t * 32 + lr;
+        const int qrow = myq < q1 ? myq : q1 - 1;   // tail lanes compute on a valid row
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int ks = 0; ks < KS; ++ks)
+            qf[ks] = *(const bf16x8*)(qkv + (size_t)qrow * ld3 + h * DH + ks * 16 + hl * 8);
+    };
+    const int t0 = part + wave * a.parts;
+    bf16x8 qf[KS];
+    load_q(t0, qf);
+    for (int c0 = tid; c0 < total; c0 += SU * NT) {
+        size_t rowoff[SU];
+        u32x4 kv[SU], vv[SU];
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
             const int c = min(c0 + u * NT, total - 1);
             const int j = min(c / CH, N - 1);
             rowoff[u] = (size_t)a.pos[(size_t)f * N + j] * ld3 + h * DH + (c % CH) * 8;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < SU; ++u) {
             kv[u] = *(const u32x4*)(qkv + rowoff[u] + D);
             vv[u] = *(const u32x4*)(qkv + rowoff[u] + 2 * D);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < SU; ++u) {
             const int c = c0 + u * NT;
             if (c < total) {
                 const int j = c / CH, part = c % CH;
@@ -497,13 +514,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char*
 
     float m, l;   // the probabilities' scale (raw score units) and their sum
     f32x16 o[DB];
-    for (int t = wave; t < ntile; t += AW) {
+    for (int t = t0; t < ntile; t += AW * a.parts) {
+        if (t != t0) load_q(t, qf);
         const int myq = q0 + t * 32 + lr;
-        const int qrow = myq < q1 ? myq : q1 - 1;   // tail lanes compute on a valid row
-        bf16x8 qf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            qf[ks] = *(const bf16x8*)(qkv + (size_t)qrow * ld3 + h * DH + ks * 16 + hl * 8);
         attend_tile<DH>(g, Ks, Vs, N, lane, qf, [](int k) { return k; }, m, l, o, [](int) {});
         if (myq < q1) store_row<DH>((uint16_t*)a.out + (size_t)myq * D + h * DH, lane, l, o);
     }
@@ -1042,11 +1055,19 @@ void launch_bf16(const AttnArgs& a0, hipStream_t s) {
     if constexpr (DH == 64) {
         if (a.G > 1 && a.cus > 0) {
             // groups of several frames: per-unit blocks, one per compute unit, when the
-            // reference rows, the maps and at least one other frame's rows fit in LDS
+            // reference rows, the maps and at least one other frame's rows fit in LDS.  With fewer
+            // units than half of the compute units (small batches; groups of at most 4 frames,
+            // which share a reference's keys among few: than all of them) most of the chip would
+            // idle: per-frame blocks then.  Measured, per-unit against per-frame blocks, us a layer:
+            // 32 units of 8 frames 27.6 / 12.5; 128 of 8 (80 % reuse) 35 / 40; 192 of 4 (50 %)
+            // 25.7 / 22.6; 512 of 8 (90 %) 60 / 143.
             const int pcap = unit_pcap(a.N, DH, a.G, 160 * 1024);
-            if (pcap >= a.N && cfg != 1 && cfg != 2) {
+            const int units = (a.F + a.G - 1) / a.G * a.H;
+            if (units * 2 < a.cus || (a.G <= 4 && units < a.cus)) {
+                a.G = 0;
+                a.sparse = 0;
+            } else if (pcap >= a.N && cfg != 1 && cfg != 2) {
                 const size_t lds = UnitGeo(a.N, DH, a.G, pcap).bytes();
-                const int units = (a.F + a.G - 1) / a.G * a.H;
                 hipLaunchKernelGGL(attn_unit_k<DH>, dim3(std::min(units, a.cus)), dim3(UW * 64),
                                    lds, s, a, pcap);
                 return;
@@ -1060,13 +1081,16 @@ void launch_bf16(const AttnArgs& a0, hipStream_t s) {
             // every frame per tile 91 / 73 / 51 / 31.  A per-unit kernel over chunks of 64 keys
             // (the reference's chunk rows staged once for the frames of a pass) took 125 / 105 /
             // 89 / 66 ms: its per-chunk barriers serialise staging and the softmax.
-            if (cfg != 3) {
+            else if (cfg != 3) {
                 a.G = 0;
                 a.sparse = 1;
                 tcut = cut >= 0 ? cut : 3;
             }
         }
     }
+    // Few frames (as many heads of frames as compute units, or fewer) go to per-frame blocks
+    // alone, several blocks to a frame's tiles (4-frame stream calls: 15.6 us a layer with the rule
+    // below, 12.6 us).
     // Reuse on without per-group blocks (head dim 64): frames with at most `tcut` query tiles go
     // to per-tile wavefronts streaming K/V (one pass over the keys per tile), the others to
     // per-frame blocks (one staging of the keys for all tiles); of the cuts 2, 3, 4 and 5,
@@ -1075,7 +1099,7 @@ void launch_bf16(const AttnArgs& a0, hipStream_t s) {
     // streams its keys once (attention 3.73 / 3.57 / 2.57 ms against 3.75 / 3.67 / 2.70 with
     // one tile per wavefront).
     if constexpr (DH == 64) {
-        if (a.G == 0 && cfg != 1 && (a.sparse || cfg == 2)) {
+        if (a.G == 0 && cfg != 1 && ((a.sparse && a.F * a.H > a.cus) || cfg == 2)) {
             a.tile_cut = cfg == 2 ? (a.N + 31) / 32 : tcut;
             if (pair) launch_wave<DH, 2>(a, s);
             else launch_wave<DH, 1>(a, s);
@@ -1098,8 +1122,14 @@ void launch_bf16(const AttnArgs& a0, hipStream_t s) {
     // frames and others with many recomputed tokens) are spread by the dispatcher, where resident
     // blocks striding over the items would give all of them to a few blocks.
     int grid = items;
-    if (a.cus > 0 && per_cu > 0 && a.tile_cut == 0)
-        grid = std::min(grid, (a.cus * per_cu + 7) / 8 * 8);
+    a.parts = 1;
+    if (a.cus > 0 && per_cu > 0 && a.tile_cut == 0) {
+        const int slots = (a.cus * per_cu + 7) / 8 * 8;
+        // fewer items than resident blocks: an item's query tiles are dealt to several blocks, at
+        // least two tiles to each in a frame without reuse
+        if (a.G == 0) a.parts = std::max(1, std::min(slots / items, ((a.N + 31) / 32 + 1) / 2));
+        grid = std::min(grid * a.parts, slots);
+    }
     hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(grid), dim3(AW * 64), lds, s, a);
 }
 

@@ -145,6 +145,7 @@ struct AttnArgs {
     int sparse;        // reuse on with G == 0: frames hold few query tiles (per-tile wavefronts)
     int tile_cut;      // set by launch_attention: frames with at most this many query tiles go to
                        // per-tile wavefronts, the others to per-frame blocks
+    int parts;         // set by launch_attention: blocks a frame and head's query tiles are dealt to
 };
 void launch_attention(bool bf16, const AttnArgs& a, hipStream_t s);
 // Class-token attention weights of every non-reference frame (G > 0: frames f % G == 0 are

@@ -64,3 +64,31 @@ def test_fp32_tiles_bitwise(S, p, D, H, n):
     ref = oracle.dense_vit(fr[-2:], blob, m.as_dict(), return_tokens=True)
     check_close(host(got[0])[-2:], ref[0], "f32", "embeddings")
     check_close(host(got[2])[-2:], ref[1], "f32", "tokens")
+
+
+@pytest.mark.parametrize("G", [4, 8])
+def test_attention_routes_bitwise(G):
+    """Per-group blocks (at least 256 and 128 pairs of a group and a head), per-frame blocks with a
+    frame's query tiles dealt to several of them (internal batches of two groups; streamed calls of
+    five frames): the same bits."""
+    torch = require_gpu()
+    m = ModelConfig(112, 16, 2, 256, 4, 512, "bf16")
+    n = 264
+    blob = synth.make_blob(m, 55)
+    rng = np.random.default_rng(56)
+    fr = rng.standard_normal((n, 3, 112, 112)).astype(np.float32)
+    for f in range(n):   # patches of each group's first frame, a third of them with noise
+        keep = rng.random((1, 7, 1, 7, 1)) < 0.66
+        own, ref = (fr[k].reshape(3, 7, 16, 7, 16) for k in (f, f // G * G))
+        fr[f] = np.where(keep, ref + 0.05 * own, own).reshape(3, 112, 112)
+    fr = dev(fr)
+    big = encoder(m, blob, n)
+    want = big.encode(fr, G, 0.9, want_tokens=True)
+    few = encoder(m, blob, 2 * G).encode(fr, G, 0.9, want_tokens=True)
+    parts = [big.stream_encode(fr[f:f + 5], G, 0.9, want_tokens=True) for f in range(0, n, 5)]
+    torch.cuda.synchronize()
+    reuse = host(want[1]).mean()
+    assert 0.2 < reuse < 0.8, reuse
+    for k in range(3):
+        assert np.array_equal(host(want[k]), host(few[k])), k
+        assert np.array_equal(host(want[k]), np.concatenate([host(p[k]) for p in parts])), k
