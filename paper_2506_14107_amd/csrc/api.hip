@@ -543,10 +543,9 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
         at.N = N;
         at.D = D;
         at.H = d.H;
-        // per-group blocks assume the star with the reference's rows packed in the batch
-        at.G = (dense || reord || skip > 0) ? 0 : G;
+        at.G = dense ? 0 : G;
+        at.star = !reord && skip == 0;   // what per-group blocks assume
         at.skip = skip;
-        at.sparse = !dense;
         at.cus = h->cus;
         {
             Scope sc(h, DV_STAGE_ATTN, s);

@@ -1,13 +1,12 @@
 // Attention over mixed fresh and reference K/V.
 //
-// Per-frame kernel: one block per (frame f, head h).  The block stages the frame's N keys and
-// values of head h in LDS, reading each key row through pos[]: a recomputed token's own packed
-// row, or -- for a reused token -- the packed row of the same token of the reference frame.
-// The frame's packed query rows qoff[f] .. qoff[f+1] are cut into tiles of 32 that the
-// block's wavefronts take in turn.  Per-unit kernel (star groups): the reference's keys are
-// staged once for all frames of a group.  Per-tile kernel (reuse without groups: reordering,
-// stream calls): a wavefront takes one or two query tiles of a frame and streams the keys
-// through its own LDS buffer.
+// Each key row is read through pos[]: a recomputed token's own packed row, or -- for a reused token
+// -- the packed row of the same token of the frame it is reused from.  Three bf16 kernels share one
+// softmax loop (attend_tile), one query tile of 32 per wavefront:
+//   streamed (attn_stream_k)   four tiles of a frame and head per block, keys through a small LDS ring
+//   per frame (attn_mfma_k)    all keys of a frame and head in LDS, its tiles over eight wavefronts
+//   per unit (attn_unit_k)     star groups: the reference's keys in LDS once for a group's frames
+// launch_bf16 says which runs when, and why.
 //
 // bf16 path (MFMA 32x32x16, fp32 accumulate), every quantity kept with one query per lane:
 //   S^T = K . Q^T      A = K rows from LDS, B = the query tile (registers); lane l holds the
@@ -25,7 +24,6 @@
 //
 // fp32 path: the same products on v_mfma_f32_16x16x4_f32 (attn_f32_k).
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "dv_internal.h"
@@ -251,143 +249,6 @@ __device__ __forceinline__ void attend_tile(const Geo& g, const uint16_t* Ks, co
     for (; kb < nkb; kb += 2) step(kb, std::integral_constant<bool, true>());
 }
 
-// attend_tile for up to NQ query tiles of one frame at once (nq of them present): every step's
-// keys and values are staged once for all of them; each tile's arithmetic, in its order, is
-// attend_tile's, so its results are the same bit for bit.
-template <int DH, int NQ, class KRow, class Stage>
-__device__ __forceinline__ void attend_tiles(const Geo& g, const uint16_t* Ks, const uint16_t* Vs,
-                                             int N, int lane, const bf16x8 (&qf)[NQ][DH / 16],
-                                             int nq, KRow krow, float (&m)[NQ], float (&l)[NQ],
-                                             f32x16 (&o)[NQ][(DH + 31) / 32], Stage stage) {
-    constexpr int KS = DH / 16;          // k-steps of S^T
-    constexpr int DB = (DH + 31) / 32;   // 32-row blocks of O^T
-    const int hl = lane >> 5, lr = lane & 31;
-    const float sl2 = 1.4426950408889634f / sqrtf((float)DH);  // log2(e) / sqrt(dh)
-    const float lazy = 8.0f / sl2;    // raw score units of a factor 2^8
-    const int nkb = g.npad / 32;
-    const int grp = lane >> 4, gi = lane & 15;    // 16-lane group of the transposing read
-    const int tr_key = hl * 4 + (gi >> 2);
-    const int tr_dim = (grp & 1) * 16 + (gi & 3) * 4;
-
-    // scores of key block kb against the query tile (raw, unscaled); MK: the block may hold
-    // keys past N
-    auto scores = [&](int q, int kb, auto mk) {
-        f32x16 sc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
-        const int row = krow(kb * 32 + lr);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 kf = *(const bf16x8*)(Ks + g.kofs(row, ks * 2 + hl));
-            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[q][ks], sc, 0, 0, 0);
-        }
-        if (decltype(mk)::value && (kb + 1) * 32 > N) {   // ragged last block: keys past N get -inf
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = kb * 32 + (r >> 2) * 8 + hl * 4 + (r & 3);
-                sc[r] = key < N ? sc[r] : -INFINITY;
-            }
-        }
-        return sc;
-    };
-    // O^T += V^T(kb) . P^T(kb)
-    auto accumulate = [&](int q, int kb, const bf16x8 (&pf)[2]) {
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            // lane (group grp, index gi) names key kb*32 + ks*16 + hl*4 + gi/4 (+8) and dims
-            // b*32 + (grp&1)*16 + 4*(gi%4); it receives dim b*32 + (grp&1)*16 + gi of the 4
-            // keys named by lanes 4e + gi/4 of its group
-            const int key = kb * 32 + ks * 16 + tr_key;
-            const int r0 = krow(key), r1 = krow(key + 8);
-#pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                int d = b * 32 + tr_dim;
-                d = d < DH ? d : DH - 4;   // head dims past DH: any finite row data
-                const uint16_t* p0 = Vs + g.vofs(r0, d >> 3) + (d & 7);
-                const uint16_t* p1 = Vs + g.vofs(r1, d >> 3) + (d & 7);
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) s16x4*)p0);
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) s16x4*)p1);
-                const s16x4 both[2] = {lo, hi};
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
-                o[q][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], o[q][b], 0, 0, 0);
-            }
-        }
-    };
-
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[q][b][r] = 0.f;
-        m[q] = -INFINITY;
-        l[q] = 0.f;
-    }
-    // one step over key blocks kb, kb + 1 for every tile; MK as in attend_tile
-    auto step = [&](int kb, auto mk) {
-        constexpr bool MK = decltype(mk)::value;
-        stage(kb);
-        const int kb1 = kb + 1;
-        const bool two = !MK || kb1 < nkb;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            if (q >= nq) break;   // wave-uniform: the tile does not exist
-            const f32x16 s0 = scores(q, kb, mk);
-            f32x16 s1;
-            if (two) {
-                s1 = scores(q, kb1, mk);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s1[r] = -INFINITY;
-            }
-            float mx[16];   // as in attend_tile: pairwise trees
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mx[r] = fmaxf(s0[r], s1[r]);
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1)
-#pragma unroll
-                for (int r = 0; r < w; ++r) mx[r] = fmaxf(mx[r], mx[r + w]);
-            float bm = mx[0];
-            bm = fmaxf(bm, other_half(bm));
-            if (__any(bm > m[q] + lazy)) {   // as in attend_tile
-                const float mn = fmaxf(m[q], bm);
-                const float alpha = __builtin_amdgcn_exp2f((m[q] - mn) * sl2);
-                l[q] *= alpha;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[q][b][r] *= alpha;
-                m[q] = mn;
-            }
-            const float nm = -m[q] * sl2;
-            float sr[16];
-            bf16x8 p0[2], p1[2];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float e0 = __builtin_amdgcn_exp2f(fmaf(s0[r], sl2, nm));
-                const float e1 = __builtin_amdgcn_exp2f(fmaf(s1[r], sl2, nm));
-                sr[r] = e0 + e1;
-                p0[r >> 3][r & 7] = (__bf16)e0;
-                p1[r >> 3][r & 7] = (__bf16)e1;
-            }
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1)
-#pragma unroll
-                for (int r = 0; r < w; ++r) sr[r] += sr[r + w];
-            const float ps = sr[0];
-            l[q] += ps + other_half(ps);
-            accumulate(q, kb, p0);
-            if (two) accumulate(q, kb1, p1);
-        }
-    };
-    const int nfull = N / 32;   // key blocks with no key past N
-    int kb = 0;
-    for (; kb + 1 < nfull; kb += 2) step(kb, std::integral_constant<bool, false>());
-    for (; kb < nkb; kb += 2) step(kb, std::integral_constant<bool, true>());
-}
-
 // o / l of a lane's query as bf16 to its output row (dims of this lane's register groups)
 template <int DH>
 __device__ __forceinline__ void store_row(uint16_t* dst, int lane, float l,
@@ -409,46 +270,24 @@ __device__ __forceinline__ void store_row(uint16_t* dst, int lane, float l,
 // ---- per-frame items ---------------------------------------------------------------------------
 // Work split: T = ceil(q/32) query tiles over AW wavefronts, each tile over all key blocks.
 template <int DH>
-__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int part, char* smem);
+__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char* smem);
 
 template <int DH>
 __global__ __launch_bounds__(AW * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 4 : 2, DH == 64 ? 4 : 2)))
 void attn_mfma_k(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // The grid holds as many blocks as are resident at once (a multiple of 8, one share per
-    // XCD) and each block walks a list of work items (frame f, head h): one item per launch slot
-    // would leave the compute units waiting on workgroup dispatch when items are short.
-    // Without groups the items are striped over the blocks, heads fastest, so that the items of a
-    // frame land on all 8 XCDs (block i runs on XCD i % 8; with frames fastest, every I frame of
-    // a reordered batch, one frame in 8, would fall on the same XCD).  With groups, a unit
-    // (a group's frames, one head) lives on XCD unit % 8, whose L2 then serves the reference
-    // rows all of its frames read; the units of XCD x are dealt to its R blocks
-    // frame-index-major (entry e = unit e % U, frame e / U of the group), so that every block
-    // takes reference and non-reference frames alike.
-    if (a.G > 0) {
-        const int units = (a.F + a.G - 1) / a.G * a.H;
-        const int x = blockIdx.x % 8, R = gridDim.x / 8, r = blockIdx.x / 8;
-        const int U = (units + 7) / 8;
-        for (int e = r; e < U * a.G; e += R) {
-            const int u = x + 8 * (e % U), j = e / U;
-            const int f = u / a.H * a.G + j;
-            if (u < units && f < a.F) attn_item<DH>(a, f, u % a.H, 0, smem);
-            lds_barrier();   // the next item restages K/V over this item's LDS
-        }
-    } else {
-        const int fh = a.F * a.H;
-        for (int item = blockIdx.x; item < fh * a.parts; item += gridDim.x) {
-            const int part = item / fh, i = item - part * fh;
-            attn_item<DH>(a, i / a.H, i % a.H, part, smem);
-            lds_barrier();
-        }
+    // The grid holds as many blocks as are resident at once and each block walks a list of work
+    // items (frame f, head h), heads fastest: one item per launch slot would leave the compute
+    // units waiting on workgroup dispatch when items are short.
+    for (int item = blockIdx.x; item < a.F * a.H; item += gridDim.x) {
+        attn_item<DH>(a, item / a.H, item % a.H, smem);
+        lds_barrier();   // the next item restages K/V over this item's LDS
     }
 }
 
-// One work item: frame f, head h, its query tiles part, part + a.parts, ...  Every thread of the
-// block takes the same path.
+// One work item: frame f, head h.  Every thread of the block takes the same path.
 template <int DH>
-__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int part, char* smem) {
+__device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char* smem) {
     constexpr int KS = DH / 16;          // k-steps of S^T
     constexpr int DB = (DH + 31) / 32;   // 32-row blocks of O^T
     constexpr int CH = DH / 8;           // 16-byte chunks per row
@@ -467,8 +306,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int p
     const uint16_t* qkv = (const uint16_t*)a.qkv;
     const int q0 = a.qoff[f], q1 = a.qoff[f + 1];
     const int ntile = (q1 - q0 + 31) / 32;
-    // none, or taken by per-tile wavefronts, or by the other parts
-    if (ntile <= a.tile_cut || part >= ntile) return;
+    if (ntile == 0) return;
 
     // stage K and V rows (row-major, 16-byte chunks); keys past N repeat key N-1 (finite data
     // whose scores are masked).  Up to SU chunks per thread are gathered before any store
@@ -483,9 +321,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int p
         for (int ks = 0; ks < KS; ++ks)
             qf[ks] = *(const bf16x8*)(qkv + (size_t)qrow * ld3 + h * DH + ks * 16 + hl * 8);
     };
-    const int t0 = part + wave * a.parts;
     bf16x8 qf[KS];
-    load_q(t0, qf);
+    load_q(wave, qf);
     for (int c0 = tid; c0 < total; c0 += SU * NT) {
         size_t rowoff[SU];
         u32x4 kv[SU], vv[SU];
@@ -514,118 +351,133 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, int p
 
     float m, l;   // the probabilities' scale (raw score units) and their sum
     f32x16 o[DB];
-    for (int t = t0; t < ntile; t += AW * a.parts) {
-        if (t != t0) load_q(t, qf);
+    for (int t = wave; t < ntile; t += AW) {
+        if (t != wave) load_q(t, qf);
         const int myq = q0 + t * 32 + lr;
         attend_tile<DH>(g, Ks, Vs, N, lane, qf, [](int k) { return k; }, m, l, o, [](int) {});
         if (myq < q1) store_row<DH>((uint16_t*)a.out + (size_t)myq * D + h * DH, lane, l, o);
     }
 }
 
-// ---- per-wavefront items (reuse on: frames with few query tiles) ------------------------------
-// A work item is one query tile (frame f, head h, tile t), taken by one wavefront on its own:
-// the frame's keys and values stream through a wavefront-private LDS buffer, 64 keys (one step
-// of attend_tile) at a time, fetched by buffer_load ... lds through pos (one instruction writes
-// 1 KiB: lane i at 16 i, so each lane fetches the chunk that belongs at its slot of the
-// swizzled layout).  Nothing is shared between wavefronts -- no barrier -- so a compute unit
-// keeps as many tiles in flight as buffers fit, where a per-frame block stages a whole frame
-// for what is mostly a single tile.  The arithmetic is attend_tile's: results equal the other
-// kernels' bit for bit.
-constexpr int SW = 4;   // wavefronts of a per-wavefront attention block
+// ---- streamed items ----------------------------------------------------------------------------
+// A block of four wavefronts takes up to four query tiles of a frame and head and streams the
+// frame's keys and values through a two-buffer ring of 64 keys (one step of attend_tile): a step's
+// rows wait in registers while the step before is computed, then go to LDS behind one barrier.  The
+// ring is small, so several blocks share a compute unit and one's barriers and load latency are
+// covered by the others' arithmetic: bound by the softmax's VALU work (577 keys, 60 % reuse: about 108
+// us a layer for 128 frames at 1336 VALU cycles a step; 168 measured).  Two or eight wavefronts a
+// block, or registers for a fourth wavefront per SIMD, were slower or equal.
+constexpr int FW = 4;   // wavefronts of a streamed block
 
 template <int DH>
-struct WaveBuf {   // 64 rows of K and 64 of V, with Geo's strides
-    static constexpr int LDK = (DH == 64 || DH == 128) ? DH : DH + 8;
-    static constexpr int LDV = (DH == 64 || DH == 128) ? DH : 96;
-    static constexpr size_t ELEMS = (size_t)64 * (LDK + LDV);
-};
-
-template <int DH, int NQ>
-__global__ __launch_bounds__(SW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_wave_k(AttnArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+__global__ __launch_bounds__(FW * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 3 : 2, DH == 64 ? 3 : 2)))
+void attn_stream_k(AttnArgs a, int qblocks) {
     constexpr int KS = DH / 16;
     constexpr int DB = (DH + 31) / 32;
+    constexpr int CH = DH / 8;                       // 16-byte chunks per row
+    constexpr int NT = FW * 64;
+    constexpr int PC = (64 * CH + NT - 1) / NT;      // chunks of K (and of V) per thread and step
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int N = a.N, D = a.D;
     const Geo g(N, DH);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint16_t* Ks = (uint16_t*)smem;
+    uint16_t* Vs = Ks + (size_t)128 * g.ldk;
+    // a unit (a group's frames, one head) lives on one XCD, its blocks one after another, so that
+    // the XCD's L2 serves the reference rows its frames share
+    const int G = a.G > 0 ? a.G : 1;
+    const int units = (a.F + G - 1) / G * a.H;
+    const int e = blockIdx.x / 8, per = G * qblocks;
+    const int u = e / per * 8 + blockIdx.x % 8, w_in = e % per;
+    const int f = u / a.H * G + w_in / qblocks, h = u % a.H, qb = w_in % qblocks;
+    if (u >= units || f >= a.F) return;
+    const int q0 = a.qoff[f], q1 = a.qoff[f + 1];
+    const int ntile = (q1 - q0 + 31) / 32;
+    const int nb = (ntile + FW - 1) / FW;            // blocks the tiles are dealt to
+    if (qb >= nb) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hl = lane >> 5, lr = lane & 31;
-    using WB = WaveBuf<DH>;
-    uint16_t* Ks = (uint16_t*)smem + (size_t)wave * WB::ELEMS;
-    uint16_t* Vs = Ks + (size_t)64 * WB::LDK;
     const size_t ld3 = 3 * (size_t)D;
-    const uint16_t* qkv = (const uint16_t*)a.qkv;
-    // the packed K/V rows (and the cached reference's rows past them) are below 2^32 bytes
-    const __amdgpu_buffer_rsrc_t rq =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.qkv), (short)0, (int)0xFFFFFFF0u,
-                                          0x00020000);
-    static_assert(DH == 64, "rows of 8 16-byte slots, K and V alike");
-    constexpr int KI = 8;   // copy instructions per step for K, and as many for V
-    // an item is NQ consecutive query tiles of a frame, t .. t + nq - 1
-    const int tmax = ((N + 31) / 32 + NQ - 1) / NQ;
-    const int items = a.F * a.H * tmax;
-    for (int item = blockIdx.x * SW + wave; item < items; item += gridDim.x * SW) {
-        const int t = item % tmax * NQ, fh = item / tmax;
-        const int f = fh / a.H, h = fh % a.H;
-        const int q0 = a.qoff[f], q1 = a.qoff[f + 1];
-        if (t * 32 >= q1 - q0 || q1 - q0 > a.tile_cut * 32) continue;   // none, or a per-frame block
-        const int nq = min(NQ, (q1 - q0 + 31) / 32 - t);
-        const int* pf = a.pos + (size_t)f * N;
-        const uint32_t hoff = (uint32_t)(h * DH) * 2;
-        // Lane l fetches row r = u*8 + l/8 of instruction u, slot l%8 (K and V rows have the same
-        // 8 slots); prow holds those rows' byte offsets for the coming step, loaded one step
-        // ahead so that a step waits for one memory round trip (the copy), not two.
-        uint32_t prow[KI];
-        auto rows = [&](int kb, uint32_t (&dst)[KI]) {
+    const uint16_t* qkv = (const uint16_t*)a.qkv + (size_t)h * DH;
+    const int t = qb + wave * nb;
+    const int myq = q0 + t * 32 + lr;
+    const int qrow = myq < q1 ? myq : q1 - 1;        // tail lanes compute on a valid row
+    bf16x8 qf[KS];
 #pragma unroll
-            for (int u = 0; u < KI; ++u)
-                dst[u] = (uint32_t)pf[min(kb * 32 + u * 8 + (lane >> 3), N - 1)] *
-                             (uint32_t)(ld3 * 2) + hoff;
-        };
-        rows(0, prow);
-        // keys kb*32 .. kb*32 + 63 (past N: key N-1, finite data whose scores are masked) into
-        // the buffer; LDS row = key - kb*32, the low bits of the key as attend_tile's krow needs
-        auto stage = [&](int kb) {
-            uint32_t next[KI];
-            rows(kb + 2, next);
-            __builtin_amdgcn_s_waitcnt(0xc07f);   // this wave's reads of the last step are done
-            asm volatile("" ::: "memory");
+    for (int ks = 0; ks < KS; ++ks)
+        qf[ks] = *(const bf16x8*)(qkv + (size_t)qrow * ld3 + ks * 16 + hl * 8);
+
+    const int* pos = a.pos + (size_t)f * N;
+    // the packed rows are below 2^32 bytes and 2^24 in number: 32-bit byte offsets, 24-bit products
+    const auto rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.qkv), (short)0,
+                                                      (int)0xFFFFFFF0u, 0x00020000);
+    uint32_t prow[PC], kofs[PC], vofs[PC], coff[PC];
+    int key[PC];
 #pragma unroll
-            for (int u = 0; u < KI; ++u) {
-                const int r = u * 8 + (lane >> 3), sl = lane & 7;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rq, (__attribute__((address_space(3))) void*)(Ks + u * 512), 16,
-                    (int)(prow[u] + (uint32_t)D * 2 + (sl ^ ((r >> 1) & 7)) * 16), 0, 0, 0);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rq, (__attribute__((address_space(3))) void*)(Vs + u * 512), 16,
-                    (int)(prow[u] + (uint32_t)D * 4 + (sl ^ (2 * ((r >> 1) & 3))) * 16), 0, 0,
-                    0);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the step has landed
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int u = 0; u < KI; ++u) prow[u] = next[u];
-        };
-        bf16x8 qf[NQ][KS];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int myq = q0 + (t + q) * 32 + lr;
-            const int qrow = myq < q1 ? myq : q1 - 1;   // tail lanes compute on a valid row
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                qf[q][ks] = *(const bf16x8*)(qkv + (size_t)qrow * ld3 + h * DH + ks * 16 + hl * 8);
-        }
-        float m[NQ], l[NQ];
-        f32x16 o[NQ][DB];
-        attend_tiles<DH, NQ>(g, Ks, Vs, N, lane, qf, nq, [](int k) { return k & 63; }, m, l, o,
-                             stage);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int myq = q0 + (t + q) * 32 + lr;
-            if (q < nq && myq < q1)
-                store_row<DH>((uint16_t*)a.out + (size_t)myq * D + h * DH, lane, l[q], o[q]);
-        }
+    for (int p = 0; p < PC; ++p) {
+        const int i = min(tid + p * NT, 64 * CH - 1), r = i / CH, c = i % CH;
+        key[p] = r;
+        kofs[p] = g.kofs(r, c);
+        vofs[p] = g.vofs(r, c);
+        coff[p] = (h * DH + D + c * 8) * 2;
     }
+    u32x4 kv[PC], vv[PC];
+    auto rows = [&](int k0) {   // packed rows of keys k0 .. k0 + 63 (past N: key N - 1, masked)
+#pragma unroll
+        for (int p = 0; p < PC; ++p) prow[p] = pos[min(k0 + key[p], N - 1)];
+    };
+    auto load = [&]() {
+#pragma unroll
+        for (int p = 0; p < PC; ++p) {
+            const uint32_t off = __umul24(prow[p], 6 * D) + coff[p];
+            kv[p] = __builtin_amdgcn_raw_buffer_load_b128(rq, (int)off, 0, 0);
+            vv[p] = __builtin_amdgcn_raw_buffer_load_b128(rq, (int)off, 2 * D, 0);
+        }
+    };
+    rows(0);
+    load();
+    rows(64);
+    // before the step of keys k0 .. k0 + 63: every wave has finished the step two before (it passed
+    // the last barrier after it), so that step's buffer is free
+    auto stage = [&](int kb) {
+        const int k0 = kb * 32;
+        uint16_t* const Kb = Ks + (k0 & 64) * g.ldk;
+        uint16_t* const Vb = Vs + (k0 & 64) * g.ldv;
+#pragma unroll
+        for (int p = 0; p < PC; ++p)
+            if (64 * CH % NT == 0 || tid + p * NT < 64 * CH) {
+                *(u32x4*)(Kb + kofs[p]) = kv[p];
+                *(u32x4*)(Vb + vofs[p]) = vv[p];
+            }
+        if (k0 + 64 < N) {
+            load();
+            rows(k0 + 128);
+        }
+        lds_barrier();
+    };
+    if (t < ntile) {
+        float m, l;
+        f32x16 o[DB];
+        attend_tile<DH>(g, Ks, Vs, N, lane, qf, [](int k) { return k & 127; }, m, l, o, stage);
+        if (myq < q1) store_row<DH>((uint16_t*)a.out + (size_t)myq * D + h * DH, lane, l, o);
+    } else {
+        for (int kb = 0; kb < g.npad / 32; kb += 2) stage(kb);   // the block's barriers and copies
+    }
+}
+
+template <int DH>
+void launch_stream(const AttnArgs& a, hipStream_t s) {
+    const Geo g(a.N, DH);
+    const size_t lds = (size_t)128 * (g.ldk + g.ldv) * 2;
+    static bool raised = false;
+    if (!raised) {
+        (void)hipFuncSetAttribute((const void*)attn_stream_k<DH>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        raised = true;
+    }
+    const int G = a.G > 0 ? a.G : 1, qblocks = ((a.N + 31) / 32 + FW - 1) / FW;
+    const int units = (a.F + G - 1) / G * a.H;
+    hipLaunchKernelGGL(attn_stream_k<DH>, dim3((units + 7) / 8 * 8 * G * qblocks), dim3(FW * 64), lds,
+                       s, a, qblocks);
 }
 
 // ---- per-unit items ----------------------------------------------------------------------------
@@ -1007,129 +859,57 @@ size_t f32_lds_bytes(int N, int dh) {
     return ((size_t)N * (dh + 1) + (size_t)N * dh + (size_t)4 * dh + (size_t)4 * N) * 4;
 }
 
-template <int DH, int NQ>
-void launch_wave(const AttnArgs& a, hipStream_t s) {
-    constexpr size_t lds = (size_t)SW * WaveBuf<DH>::ELEMS * 2;
-    static int per_cu = -1;
-    if (per_cu < 0) {
-        (void)hipFuncSetAttribute((const void*)attn_wave_k<DH, NQ>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        int v = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, (const void*)attn_wave_k<DH, NQ>,
-                                                         SW * 64, lds) != hipSuccess)
-            v = 0;
-        per_cu = v;
-    }
-    const int items = a.F * a.H * (((a.N + 31) / 32 + NQ - 1) / NQ);
-    int grid = (items + SW - 1) / SW;
-    if (a.cus > 0 && per_cu > 0) grid = std::min(grid, a.cus * per_cu);
-    hipLaunchKernelGGL((attn_wave_k<DH, NQ>), dim3(grid), dim3(SW * 64), lds, s, a);
-}
-
+// Which kernel: the same bits from each (one arithmetic per query), so the rule is about time alone.
+//   per unit   head dim 64, star groups whose reference rows leave LDS for another frame's, and
+//              units (groups x heads, one block per compute unit) that fill their rounds to 9/10: the
+//              reference's keys are staged once per group.
+//   per frame  more frames x heads than blocks are resident, and either head dim 64 with two
+//              blocks' keys per compute unit (up to 320 keys) without reuse or in groups of at most 4,
+//              or head dim 128 (one block; 64 frames of 8 heads at 90 % 31 us a layer, streamed 34).
+//   streamed   everything else: few frames, ungrouped reuse (reordering, stream calls), head dims 80
+//              and 96 or long key rows (a frame's keys fill most of LDS, eight wavefronts a unit).
+// Measured, us a layer, streamed / per frame / per unit (bf16, ViT-L/14 unless named): 256 frames
+// in groups of 8 at 50 % reuse 143 / - / 127, 90 % 80 / 143 / 57; 192 frames (1.5 rounds of units) 113 /
+// - / 138 and 73 / - / 68; 64 frames 42 / - / 64 and 29 / - / 33; reuse off, 8 frames 15 / 16 (66 without
+// several blocks to a frame), 128 frames 121 / 105; 336 px (577 keys) 60 % 168 / 222 / -, 90 % 94 / 140;
+// ViT-H/14 (head dim 80) 53 / 62; ViT-B/16, 64 frames in groups of 4, 24.5 / 22.5 / 25.7; reordered 256
+// frames at 90 % 86 / 114 (with a streaming wavefront per tile for short frames).
 template <int DH>
-void launch_bf16(const AttnArgs& a0, hipStream_t s) {
-    AttnArgs a = a0;
-    a.tile_cut = 0;
-    static bool raised = false;
-    if (!raised) {  // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
+void launch_bf16(const AttnArgs& a, hipStream_t s) {
+    static int per_cu = -1;
+    const size_t lds = Geo(a.N, DH).bytes();
+    if (per_cu < 0) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
         (void)hipFuncSetAttribute((const void*)attn_mfma_k<DH>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if constexpr (DH == 64)
             (void)hipFuncSetAttribute((const void*)attn_unit_k<DH>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        raised = true;
-    }
-    // DV_ATTN_CFG (measurements): 1 per-frame blocks only, 2 per-tile wavefronts only, also
-    // without reuse, 3 groups too large for per-unit blocks on per-frame blocks placed by unit;
-    // DV_ATTN_CUT overrides the cuts below, DV_ATTN_PAIR=0 takes one tile per wavefront.
-    static int cfg = -1, cut = -1, pair = 1;
-    if (cfg < 0) {
-        const char* e = getenv("DV_ATTN_CFG");
-        cfg = e ? atoi(e) : 0;
-        const char* c = getenv("DV_ATTN_CUT");
-        if (c) cut = std::max(0, atoi(c));
-        const char* pp = getenv("DV_ATTN_PAIR");
-        if (pp) pair = atoi(pp);
-    }
-    int tcut = cut >= 0 ? cut : 2;
-    if constexpr (DH == 64) {
-        if (a.G > 1 && a.cus > 0) {
-            // groups of several frames: per-unit blocks, one per compute unit, when the
-            // reference rows, the maps and at least one other frame's rows fit in LDS.  With fewer
-            // units than half of the compute units (small batches; groups of at most 4 frames,
-            // which share a reference's keys among few: than all of them) most of the chip would
-            // idle: per-frame blocks then.  Measured, per-unit against per-frame blocks, us a layer:
-            // 32 units of 8 frames 27.6 / 12.5; 128 of 8 (80 % reuse) 35 / 40; 192 of 4 (50 %)
-            // 25.7 / 22.6; 512 of 8 (90 %) 60 / 143.
-            const int pcap = unit_pcap(a.N, DH, a.G, 160 * 1024);
-            const int units = (a.F + a.G - 1) / a.G * a.H;
-            if (units * 2 < a.cus || (a.G <= 4 && units < a.cus)) {
-                a.G = 0;
-                a.sparse = 0;
-            } else if (pcap >= a.N && cfg != 1 && cfg != 2) {
-                const size_t lds = UnitGeo(a.N, DH, a.G, pcap).bytes();
-                hipLaunchKernelGGL(attn_unit_k<DH>, dim3(std::min(units, a.cus)), dim3(UW * 64),
-                                   lds, s, a, pcap);
-                return;
-            }
-            // Otherwise (ViT-L/14 at 336 px: 577 keys) the frames go the way of ungrouped
-            // reuse: those with few query tiles to per-tile wavefronts, which read the
-            // reference's keys and values through L2 (every frame of a group reads the same
-            // rows), the others to per-frame blocks.  Measured at 0 / 34 / 62 / 90 % reuse
-            // (attention per 1024-frame encode): per-frame blocks placed by unit 74 / 64 / 56 /
-            // 46 ms; cut 2 76 / 63 / 50 / 37; cut 3 78 / 61 / 47 / 35; cut 5 78 / 61 / 51 / 35;
-            // every frame per tile 91 / 73 / 51 / 31.  A per-unit kernel over chunks of 64 keys
-            // (the reference's chunk rows staged once for the frames of a pass) took 125 / 105 /
-            // 89 / 66 ms: its per-chunk barriers serialise staging and the softmax.
-            else if (cfg != 3) {
-                a.G = 0;
-                a.sparse = 1;
-                tcut = cut >= 0 ? cut : 3;
-            }
-        }
-    }
-    // Few frames (as many heads of frames as compute units, or fewer) go to per-frame blocks
-    // alone, several blocks to a frame's tiles (4-frame stream calls: 15.6 us a layer with the rule
-    // below, 12.6 us).
-    // Reuse on without per-group blocks (head dim 64): frames with at most `tcut` query tiles go
-    // to per-tile wavefronts streaming K/V (one pass over the keys per tile), the others to
-    // per-frame blocks (one staging of the keys for all tiles); of the cuts 2, 3, 4 and 5,
-    // 2 gave the shortest attention at 50, 70 and 90 % reuse (ViT-L/14, reordered groups of 8).
-    // A wavefront takes two consecutive tiles of a frame at a time, so that a two-tile frame
-    // streams its keys once (attention 3.73 / 3.57 / 2.57 ms against 3.75 / 3.67 / 2.70 with
-    // one tile per wavefront).
-    if constexpr (DH == 64) {
-        if (a.G == 0 && cfg != 1 && ((a.sparse && a.F * a.H > a.cus) || cfg == 2)) {
-            a.tile_cut = cfg == 2 ? (a.N + 31) / 32 : tcut;
-            if (pair) launch_wave<DH, 2>(a, s);
-            else launch_wave<DH, 1>(a, s);
-            if (a.tile_cut >= (a.N + 31) / 32) return;   // no frame left for per-frame blocks
-        }
-    }
-    const size_t lds = Geo(a.N, DH).bytes();
-    // work items: (frame, head) pairs; with reuse, the slots of whole units on each of 8 XCDs
-    const int items = a.G > 0 ? xcd_unit_grid((a.F + a.G - 1) / a.G * a.H, a.G) : a.F * a.H;
-    static int per_cu = -1;
-    if (per_cu < 0) {
         int v = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, (const void*)attn_mfma_k<DH>, AW * 64,
                                                          lds) != hipSuccess)
             v = 0;
         per_cu = v;
     }
-    // a multiple of 8 blocks keeps item i on XCD i % 8, as the placement of a group's items assumes.
-    // After per-tile wavefronts took the small frames, one block per item: the frames left (I
-    // frames and others with many recomputed tokens) are spread by the dispatcher, where resident
-    // blocks striding over the items would give all of them to a few blocks.
-    int grid = items;
-    a.parts = 1;
-    if (a.cus > 0 && per_cu > 0 && a.tile_cut == 0) {
-        const int slots = (a.cus * per_cu + 7) / 8 * 8;
-        // fewer items than resident blocks: an item's query tiles are dealt to several blocks, at
-        // least two tiles to each in a frame without reuse
-        if (a.G == 0) a.parts = std::max(1, std::min(slots / items, ((a.N + 31) / 32 + 1) / 2));
-        grid = std::min(grid * a.parts, slots);
+    const int items = a.F * a.H;
+    const int units = a.G > 1 ? (a.F + a.G - 1) / a.G * a.H : 0;
+    if constexpr (DH == 64) {
+        if (a.star && a.G > 1 && a.cus > 0) {
+            const int pcap = unit_pcap(a.N, DH, a.G, 160 * 1024);
+            if (pcap >= a.N && units * 10 >= (units + a.cus - 1) / a.cus * a.cus * 9) {
+                hipLaunchKernelGGL(attn_unit_k<DH>, dim3(std::min(units, a.cus)), dim3(UW * 64),
+                                   UnitGeo(a.N, DH, a.G, pcap).bytes(), s, a, pcap);
+                return;
+            }
+        }
     }
+    bool frame = a.cus > 0 && items > (DH == 128 ? 1 : 2) * a.cus;
+    if (DH == 64) frame = frame && 2 * lds <= 160 * 1024 && (a.G <= 1 || (a.star && a.G <= 4));
+    else frame = frame && DH == 128;
+    if (!frame) {
+        launch_stream<DH>(a, s);
+        return;
+    }
+    const int grid = per_cu > 0 ? std::min(items, a.cus * per_cu) : items;
     hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(grid), dim3(AW * 64), lds, s, a);
 }
 

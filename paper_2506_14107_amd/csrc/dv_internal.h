@@ -16,13 +16,6 @@ __host__ __device__ inline float bf16_to_f32(uint16_t h) {
     return __builtin_bit_cast(float, (uint32_t)h << 16);
 }
 
-// ---- placement of a group's frames on one XCD -------------------------------------------------
-// Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), and each XCD has
-// its own L2.  A unit of G work items that read the same reference-frame rows (the G frames of
-// one group, one head) is placed on one XCD: units u = x, x + 8, ... on XCD x.  Slots for
-// `units` units of G items each, in whole rounds of 8:
-inline int xcd_unit_grid(int units, int G) { return (units + 7) / 8 * 8 * G; }
-
 // ---- reordered referencing (I/P/B frames with past and future references) --------------------
 // Groups of G frames (G a multiple of 4) start with an I frame, computed in full.  Positions
 // 4, 8, ... of a group are P frames referencing the anchor four frames back.  Between two
@@ -139,13 +132,10 @@ struct AttnArgs {
     const int* qoff;   // [F+1] packed query rows of frame f: qoff[f] .. qoff[f+1]
     void* out;         // [M, D] elem
     int F, N, D, H;
-    int G;             // group size, 0 without reuse (block placement only)
-    int cus;           // compute units of the device (0: one block per work item)
+    int G;             // group size, 0 without reuse
+    int cus;           // compute units of the device (0: unknown)
     int skip;          // leading frames carried over from an earlier call (no rows, no queries)
-    int sparse;        // reuse on with G == 0: frames hold few query tiles (per-tile wavefronts)
-    int tile_cut;      // set by launch_attention: frames with at most this many query tiles go to
-                       // per-tile wavefronts, the others to per-frame blocks
-    int parts;         // set by launch_attention: blocks a frame and head's query tiles are dealt to
+    bool star;         // every frame's reused keys are its group's first frame's, packed in this batch
 };
 void launch_attention(bool bf16, const AttnArgs& a, hipStream_t s);
 // Class-token attention weights of every non-reference frame (G > 0: frames f % G == 0 are

@@ -66,14 +66,14 @@ def test_fp32_tiles_bitwise(S, p, D, H, n):
     check_close(host(got[2])[-2:], ref[1], "f32", "tokens")
 
 
-@pytest.mark.parametrize("G", [4, 8])
-def test_attention_routes_bitwise(G):
-    """Per-group blocks (at least 256 and 128 pairs of a group and a head), per-frame blocks with a
-    frame's query tiles dealt to several of them (internal batches of two groups; streamed calls of
-    five frames): the same bits."""
+@pytest.mark.parametrize("G,n", [(8, 480), (4, 240), (4, 264)],
+                         ids=["unit-G8", "unit-G4", "frame-G4"])
+def test_attention_routes_bitwise(G, n):
+    """Per-unit blocks (240 pairs of a group and a head), per-frame blocks (264 pairs, two rounds of
+    units mostly empty) and streamed blocks (internal batches of two groups; streamed calls of five
+    frames): the same bits."""
     torch = require_gpu()
     m = ModelConfig(112, 16, 2, 256, 4, 512, "bf16")
-    n = 264
     blob = synth.make_blob(m, 55)
     rng = np.random.default_rng(56)
     fr = rng.standard_normal((n, 3, 112, 112)).astype(np.float32)
