@@ -2,7 +2,7 @@
 //
 // Per internal batch of whole groups (layer-wise scheduling: one layer over every frame of
 // the batch before the next), the launch sequence is
-//   im2col -> patch GEMM (+bias +pos) ; class-token rows
+//   im2col (and class-token rows) -> patch GEMM (+bias +pos)
 //   for each layer:
 //     gate (cosine to the reference, or injected map) + per-frame counts
 //     compaction (idx / pos / qoff / M, all on the device)
@@ -412,11 +412,12 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
     {   // patch embedding + class-token rows
         Scope sc(h, DV_STAGE_PATCH, s);
         if (npend > 0)
-            launch_im2col(bf, pend, npend, d.S, d.p, d.Kp, wk.A, s);
+            launch_im2col(bf, pend, npend, d.S, d.p, d.Kp, wk.A, xs, h->cls, h->pos, D,
+                          h->cus, s);
         if (F - skip > npend)
             launch_im2col(bf, frames, F - skip - npend, d.S, d.p, d.Kp,
-                          (char*)wk.A + (size_t)npend * d.P * d.Kp * el, s);
-        launch_cls_init(xs, h->cls, h->pos, F - skip, N, D, s);
+                          (char*)wk.A + (size_t)npend * d.P * d.Kp * el, xs + (size_t)npend * N * D,
+                          h->cls, h->pos, D, h->cus, s);
         GemmArgs g{};
         g.A = wk.A;
         g.W = h->W_pe;
@@ -484,6 +485,7 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
             // restored rows are written out every layer; otherwise reused rows alias their root
             ga.root = (alias && l > 0) ? wk.root : nullptr;
             ga.skip = skip;
+            ga.cus = h->cus;
             launch_gate(bf, ga, s);
         }
         if (!dense) {

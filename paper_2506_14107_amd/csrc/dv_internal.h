@@ -146,10 +146,10 @@ size_t attention_lds_bytes(bool bf16, int N, int dh);
 bool attention_supported(bool bf16, int N, int dh);
 
 // ---- row kernels -----------------------------------------------------------------------------
-void launch_im2col(bool bf16, const float* frames, int F, int S, int p, int Kp, void* A,
-                   hipStream_t s);
-void launch_cls_init(float* x, const float* cls, const float* pos, int F, int N, int D,
-                     hipStream_t s);
+// Patch rows A of F frames, and their class-token rows x[f, 0, :] = cls + pos[0] (N = P + 1 rows of D
+// per frame)
+void launch_im2col(bool bf16, const float* frames, int F, int S, int p, int Kp, void* A, float* x,
+                   const float* cls, const float* pos, int D, int cus, hipStream_t s);
 
 enum GateMode : int { GATE_COS = 0, GATE_INJECT = 1, GATE_ALL = 2, GATE_NONE = 3 };
 struct GateArgs {
@@ -180,6 +180,7 @@ struct GateArgs {
                           // the cached reference (the first in the star, the last under
                           // reordering; its rows already in x), the others gaps; none is gated,
                           // and inj / out_masks start at frame skip
+    int cus;              // compute units of the device (0: unknown)
 };
 // Reordering with restoration: a reused row is built along its chain of sources; a group of G
 // frames has chains of at most G/4 + 1 reused links (B_dist1, B_dist2, then the P frames back

@@ -38,13 +38,25 @@ __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void* p, uint32_t bytes)
 }
 constexpr uint32_t ROW_SKIP = 0xFFFFFFF0u;   // an offset past every row buffer (all < 2^32 bytes)
 
+// class-token rows x[f, 0, :] = cls + pos[0] of F frames, by threads t of n
+__device__ inline void cls_rows(float* x, const float* cls, const float* pos, int F, int N, int D,
+                                size_t t, size_t n) {
+    for (size_t total = (size_t)F * D; t < total; t += n) {
+        const int f = (int)(t / D), d = (int)(t % D);
+        x[(size_t)f * N * D + d] = cls[d] + pos[d];
+    }
+}
+
 // --- patch gather: A[f*P + k, e] = frame[f][c][py*p+ky][px*p+kx], e = (c, ky, kx); zero pad to Kp
 // bf16: a thread writes 8 consecutive elements of a row with one 16-byte store (Kp is a multiple
 // of 64), walking (c, ky, kx) from the chunk's first element; 32-bit indices (F*P*Kp/8 < 2^31
 // for every batch the handle accepts)
 template <bool BF>
-__global__ void im2col_k(const float* __restrict__ frames, int F, int S, int p, int Kp, void* A) {
+__global__ void im2col_k(const float* __restrict__ frames, int F, int S, int p, int Kp, void* A,
+                         float* x, const float* cls, const float* pos, int D) {
     const int g = S / p, P = g * g, kk = 3 * p * p, pp = p * p;
+    cls_rows(x, cls, pos, F, P + 1, D, blockIdx.x * (size_t)blockDim.x + threadIdx.x,
+             (size_t)gridDim.x * blockDim.x);
     if constexpr (BF) {
         const int cpr = Kp / 8;
         const unsigned total = (unsigned)F * P * cpr;
@@ -95,12 +107,45 @@ __global__ void im2col_k(const float* __restrict__ frames, int F, int S, int p, 
     }
 }
 
-__global__ void cls_init_k(float* x, const float* cls, const float* pos, int F, int N, int D) {
-    const size_t total = (size_t)F * D;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < total;
-         t += (size_t)gridDim.x * blockDim.x) {
-        const int f = (int)(t / D), d = (int)(t % D);
-        x[(size_t)f * N * D + d] = cls[d] + pos[d];
+// The same gather (bf16, even patch size) for one strip of patches, frame f and patch row py: its
+// 3 x p pixel rows are read whole (16 bytes per lane) and kept as bf16 in LDS, from which every
+// 16-byte piece of the strip's patch rows is put together.  Bound by HBM (frames once, patch rows
+// once); gathering straight from memory reads 4 bytes per lane 32 bytes apart: 256 frames of 224 px,
+// patch 14, Kp 640: 90 -> 52 us.
+__global__ __launch_bounds__(256) void im2col_strip_k(const float* __restrict__ frames, int F, int S,
+                                                      int p, int Kp, uint16_t* A, float* x,
+                                                      const float* cls, const float* pos, int D) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    uint16_t* px = (uint16_t*)smem;   // [3 p][S]
+    const int g = S / p, kk = 3 * p * p, tid = threadIdx.x;
+    const int f = blockIdx.x / g, py = blockIdx.x - f * g;
+    cls_rows(x, cls, pos, F, g * g + 1, D, blockIdx.x * (size_t)256 + tid, (size_t)gridDim.x * 256);
+    const int q = S / 4, total = 3 * p * q;
+    for (int t = tid; t < total; t += 256) {
+        const int r = t / q, c4 = t - r * q, c = r / p, ky = r - c * p;
+        const float4 v = *(const float4*)(frames + (((size_t)f * 3 + c) * S + py * p + ky) * S + c4 * 4);
+        uint2 w;
+        w.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
+        w.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
+        *(uint2*)(px + r * S + c4 * 4) = w;
+    }
+    __syncthreads();
+    const int cpr = Kp / 8;
+    uint4* out = (uint4*)A + (size_t)(f * g + py) * g * cpr;
+    for (int t = tid; t < g * cpr; t += 256) {
+        const int k = t / cpr, e0 = (t - k * cpr) * 8;
+        int r = e0 / p, kx = e0 - r * p;   // pixel row of the strip (channel, ky) and column
+        uint32_t w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {      // pairs: p and S are even, so a pair shares its row
+            w[u] = e0 + 2 * u < kk ? *(const uint32_t*)(px + r * S + k * p + kx) : 0u;
+            kx += 2;
+            if (kx == p) {
+                kx = 0;
+                ++r;
+            }
+        }
+        out[t] = uint4{w[0], w[1], w[2], w[3]};
     }
 }
 
@@ -115,8 +160,8 @@ __global__ void cls_init_k(float* x, const float* cls, const float* pos, int F, 
 // Under reordered referencing a frame has up to two references: the similarity is the larger
 // cosine, `src` records which reference gave it (1: the future one; a tie keeps the past one),
 // and the cosines are taken in every mode but reuse-off, since they choose the source.
-template <bool BF, bool DEC, bool REORD, int CK>
-__global__ __launch_bounds__(256) void gate_k(GateArgs a) {
+template <bool BF, bool DEC, bool REORD, int CK, int NW>
+__global__ __launch_bounds__(NW * 64) void gate_k(GateArgs a) {
     const int N = a.N, D = a.D;
     const int chunks = (N + GATE_TOK - 1) / GATE_TOK;
     const int f = blockIdx.x / chunks, ch = blockIdx.x % chunks;
@@ -141,7 +186,7 @@ __global__ __launch_bounds__(256) void gate_k(GateArgs a) {
         rfut = -1;
     }
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const int nwaves = blockDim.x / WAVE;
+    constexpr int nwaves = NW;
     const int nchunk = D / 4;
     __shared__ int wcount[16];
     uint8_t* om = a.out_masks ? a.out_masks + ((size_t)(f - a.skip) * a.L + a.layer) * N : nullptr;
@@ -177,8 +222,7 @@ __global__ __launch_bounds__(256) void gate_k(GateArgs a) {
     int active = 0;
     const int i_end = min(N, (ch + 1) * GATE_TOK);
     // the previous layer's map for all of this wavefront's tokens, loaded together up front
-    // (blocks of 256 threads: GATE_TOK / 4 tokens per wavefront)
-    constexpr int TPW = GATE_TOK / 4;
+    constexpr int TPW = GATE_TOK / NW;
     uint8_t pv[TPW];
     int own_k[TPW], rp_k[TPW], rq_k[TPW];   // reordered: the tokens' roots and their anchors'
 #pragma unroll
@@ -201,8 +245,7 @@ __global__ __launch_bounds__(256) void gate_k(GateArgs a) {
     // skipped, and the same arithmetic in the same order as in the general loop below.
     bool fast = false;
     if constexpr (!DEC && !REORD && CK <= 5) {
-        fast = (a.mode == GATE_COS || a.mode == GATE_NONE) && a.d_out == nullptr &&
-               nwaves * TPW == GATE_TOK;
+        fast = (a.mode == GATE_COS || a.mode == GATE_NONE) && a.d_out == nullptr;
         if (fast) {
             const auto rx = row_rsrc(a.x, (uint32_t)((size_t)a.F * N * D * sizeof(float)));
             float4 vb[2][CK], wb[2][CK];   // the token's own row and its reference's row
@@ -830,22 +873,45 @@ __global__ __launch_bounds__(256) void restore_chain_k(float* x, const float* __
     }
 }
 
-__global__ __launch_bounds__(256) void final_ln_k(const float* x, int F, int N, int D,
-                                                  const float* g, const float* b, float* emb) {
-    const int lane = threadIdx.x & 63;
-    for (int f = (blockIdx.x * blockDim.x + threadIdx.x) / 64; f < F;
-         f += gridDim.x * blockDim.x / 64) {
-        const float* row = x + (size_t)f * N * D;
-        float s = 0.f;
-        for (int d = lane; d < D; d += 64) s += row[d];
-        const float mean = wave_sum(s) / (float)D;
-        float q = 0.f;
-        for (int d = lane; d < D; d += 64) {
-            const float a = row[d] - mean;
-            q += a * a;
+// one wavefront per frame; the class-token row is read once and kept (256 frames 13 -> 4.8 us)
+template <int CK>
+__global__ __launch_bounds__(64) void final_ln_k(const float* x, int N, int D, const float* g,
+                                                 const float* b, float* emb) {
+    const int lane = threadIdx.x, f = blockIdx.x, nchunk = D / 4;
+    const float4* row = (const float4*)(x + (size_t)f * N * D);
+    float4 v[CK], gg[CK], bb[CK];
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < CK; ++k) {
+        const int c = lane + k * 64;
+        if (c < nchunk) {
+            v[k] = row[c];
+            gg[k] = ((const float4*)g)[c];
+            bb[k] = ((const float4*)b)[c];
         }
-        const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)D + 1e-5f);
-        for (int d = lane; d < D; d += 64) emb[(size_t)f * D + d] = (row[d] - mean) * rstd * g[d] + b[d];
+    }
+#pragma unroll
+    for (int k = 0; k < CK; ++k)
+        if (lane + k * 64 < nchunk) sum += (v[k].x + v[k].y) + (v[k].z + v[k].w);
+    const float mean = wave_sum(sum) / (float)D;
+    float sq = 0.f;
+#pragma unroll
+    for (int k = 0; k < CK; ++k)
+        if (lane + k * 64 < nchunk) {
+            const float a0 = v[k].x - mean, a1 = v[k].y - mean, a2 = v[k].z - mean, a3 = v[k].w - mean;
+            sq += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
+        }
+    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + 1e-5f);
+#pragma unroll
+    for (int k = 0; k < CK; ++k) {
+        const int c = lane + k * 64;
+        if (c < nchunk) {
+            float* e = emb + (size_t)f * D + c * 4;   // the caller's: 4-byte stores
+            e[0] = (v[k].x - mean) * rstd * gg[k].x + bb[k].x;
+            e[1] = (v[k].y - mean) * rstd * gg[k].y + bb[k].y;
+            e[2] = (v[k].z - mean) * rstd * gg[k].z + bb[k].z;
+            e[3] = (v[k].w - mean) * rstd * gg[k].w + bb[k].w;
+        }
     }
 }
 
@@ -872,43 +938,58 @@ inline int grid_for(size_t work, int per_block, int cap = 8192) {
 
 }  // namespace
 
-void launch_im2col(bool bf16, const float* frames, int F, int S, int p, int Kp, void* A,
-                   hipStream_t s) {
-    const int P = (S / p) * (S / p);
+void launch_im2col(bool bf16, const float* frames, int F, int S, int p, int Kp, void* A, float* x,
+                   const float* cls, const float* pos, int D, int cus, hipStream_t s) {
+    const int g = S / p, P = g * g;
+    // strips where a pixel row is whole 16-byte pieces, a pair of patch columns stays in its row, a
+    // strip fits in LDS several times over and there are two strips per compute unit (16 frames of
+    // 224 px, one strip per unit: 10.4 us, the plain gather 6.1)
+    const size_t strip = (size_t)3 * p * S * 2;
+    if (bf16 && S % 4 == 0 && p % 2 == 0 && (uintptr_t)frames % 16 == 0 && strip <= 40 * 1024 &&
+        F * g >= 2 * cus) {
+        hipLaunchKernelGGL(im2col_strip_k, dim3(F * g), dim3(256), strip, s, frames, F, S, p, Kp,
+                           (uint16_t*)A, x, cls, pos, D);
+        return;
+    }
     const size_t total = (size_t)F * P * Kp / (bf16 ? 8 : 1);   // elements, or 8-element chunks
     const int grid = grid_for(total, 256, 65536);
-    if (bf16) hipLaunchKernelGGL(im2col_k<true>, dim3(grid), dim3(256), 0, s, frames, F, S, p, Kp, A);
-    else hipLaunchKernelGGL(im2col_k<false>, dim3(grid), dim3(256), 0, s, frames, F, S, p, Kp, A);
+    auto k = bf16 ? im2col_k<true> : im2col_k<false>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, frames, F, S, p, Kp, A, x, cls, pos, D);
 }
 
-void launch_cls_init(float* x, const float* cls, const float* pos, int F, int N, int D,
-                     hipStream_t s) {
-    hipLaunchKernelGGL(cls_init_k, dim3(grid_for((size_t)F * D, 256)), dim3(256), 0, s, x, cls,
-                       pos, F, N, D);
-}
-
-template <int CK>
-void launch_gate_ck(int v, dim3 grid, dim3 block, const GateArgs& a, hipStream_t s) {
+template <int CK, int NW>
+void launch_gate_ck(int v, dim3 grid, const GateArgs& a, hipStream_t s) {
+    const dim3 block(NW * 64);
     switch (v) {
-        case 0: hipLaunchKernelGGL((gate_k<false, false, false, CK>), grid, block, 0, s, a); break;
-        case 1: hipLaunchKernelGGL((gate_k<false, false, true, CK>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((gate_k<false, true, false, CK>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((gate_k<false, true, true, CK>), grid, block, 0, s, a); break;
-        case 4: hipLaunchKernelGGL((gate_k<true, false, false, CK>), grid, block, 0, s, a); break;
-        case 5: hipLaunchKernelGGL((gate_k<true, false, true, CK>), grid, block, 0, s, a); break;
-        case 6: hipLaunchKernelGGL((gate_k<true, true, false, CK>), grid, block, 0, s, a); break;
-        default: hipLaunchKernelGGL((gate_k<true, true, true, CK>), grid, block, 0, s, a); break;
+        case 0: hipLaunchKernelGGL((gate_k<false, false, false, CK, NW>), grid, block, 0, s, a); break;
+        case 1: hipLaunchKernelGGL((gate_k<false, false, true, CK, NW>), grid, block, 0, s, a); break;
+        case 2: hipLaunchKernelGGL((gate_k<false, true, false, CK, NW>), grid, block, 0, s, a); break;
+        case 3: hipLaunchKernelGGL((gate_k<false, true, true, CK, NW>), grid, block, 0, s, a); break;
+        case 4: hipLaunchKernelGGL((gate_k<true, false, false, CK, NW>), grid, block, 0, s, a); break;
+        case 5: hipLaunchKernelGGL((gate_k<true, false, true, CK, NW>), grid, block, 0, s, a); break;
+        case 6: hipLaunchKernelGGL((gate_k<true, true, false, CK, NW>), grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL((gate_k<true, true, true, CK, NW>), grid, block, 0, s, a); break;
     }
 }
 
 void launch_gate(bool bf16, const GateArgs& a, hipStream_t s) {
-    const dim3 grid(a.F * gate_chunks(a.N)), block(256);
+    const int blocks = a.F * gate_chunks(a.N);
     const bool dec = a.dec != nullptr && a.mode == GATE_COS;
     const int v = (bf16 ? 4 : 0) + (dec ? 2 : 0) + (a.reorder ? 1 : 0);
-    // as few float4 chunks per lane as the row needs: fewer registers, more waves per SIMD
-    if (a.D <= 1024) launch_gate_ck<4>(v, grid, block, a, s);
-    else if (a.D <= 1280) launch_gate_ck<5>(v, grid, block, a, s);
-    else launch_gate_ck<8>(v, grid, block, a, s);
+    // as few float4 chunks per lane as the row needs: fewer registers, more waves per SIMD.  Few
+    // tokens (no more blocks than two per compute unit): a wavefront per token, so that a block is
+    // one token's latency instead of four's (ViT-L/14, us a layer: 16 frames 9.4 -> 7.5, 4 frames
+    // 7.2 -> 5.3)
+    if (a.cus > 0 && blocks <= 2 * a.cus && a.D <= 1280) {
+        if (a.D <= 1024) launch_gate_ck<4, GATE_TOK>(v, dim3(blocks), a, s);
+        else launch_gate_ck<5, GATE_TOK>(v, dim3(blocks), a, s);
+    } else if (a.D <= 1024) {
+        launch_gate_ck<4, 4>(v, dim3(blocks), a, s);
+    } else if (a.D <= 1280) {
+        launch_gate_ck<5, 4>(v, dim3(blocks), a, s);
+    } else {
+        launch_gate_ck<8, 4>(v, dim3(blocks), a, s);
+    }
 }
 
 void launch_count(const uint8_t* m, int F, int N, int G, int* cnt, hipStream_t s) {
@@ -975,8 +1056,8 @@ void launch_resolve(const uint8_t* cur, const uint8_t* src, int F, int N, int G,
 
 void launch_final_ln(const float* x, int F, int N, int D, const float* g, const float* b,
                      float* emb, hipStream_t s) {
-    hipLaunchKernelGGL(final_ln_k, dim3(grid_for((size_t)F, 4)), dim3(256), 0, s, x, F, N, D, g,
-                       b, emb);
+    auto k = D <= 1024 ? final_ln_k<4> : D <= 1280 ? final_ln_k<5> : final_ln_k<8>;
+    hipLaunchKernelGGL(k, dim3(F), dim3(64), 0, s, x, N, D, g, b, emb);
 }
 
 void launch_fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s) {

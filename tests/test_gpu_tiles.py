@@ -92,3 +92,24 @@ def test_attention_routes_bitwise(G, n):
     for k in range(3):
         assert np.array_equal(host(want[k]), host(few[k])), k
         assert np.array_equal(host(want[k]), np.concatenate([host(p[k]) for p in parts])), k
+
+
+@pytest.mark.parametrize("S,p,n,shift", [(224, 14, 40, 0), (112, 16, 80, 0), (112, 16, 80, 1),
+                                         (60, 12, 110, 0), (70, 14, 110, 0), (63, 7, 70, 0)])
+def test_patch_gather_routes_bitwise(S, p, n, shift):
+    """Whole batches (strips through LDS where size, parity and alignment allow; shift: frames that
+    start 4 bytes off 16) against one frame at a time (the plain gather): the same bits."""
+    torch = require_gpu()
+    m = ModelConfig(S, p, 1, 128, 2, 128, "bf16")
+    blob = synth.make_blob(m, 57)
+    rng = np.random.default_rng(58)
+    flat = dev(rng.standard_normal(n * 3 * S * S + 4).astype(np.float32))
+    fr = flat[shift:shift + n * 3 * S * S].view(n, 3, S, S)
+    off = float("-inf")
+    got = encoder(m, blob, n).encode(fr, 1, off, want_masks=False, want_tokens=True)
+    one = encoder(m, blob, 1).encode(fr, 1, off, want_masks=False, want_tokens=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(got[0]), host(one[0]))
+    assert np.array_equal(host(got[2]), host(one[2]))
+    ref = oracle.dense_vit(host(fr)[-1:], blob, m.as_dict(), return_tokens=True)
+    check_close(host(got[2])[-1:], ref[1], "bf16", "tokens")
