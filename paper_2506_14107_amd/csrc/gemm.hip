@@ -321,20 +321,25 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
     const auto rA = buf_rsrc(a.A, BUF_ANY);
     const auto rW = buf_rsrc(a.W, BUF_ANY);
     const auto rBias = buf_rsrc(a.bias, BUF_ANY);
-    auto issue = [&](int kt) {
-        uint16_t* st = sm + (kt % S) * STAGE;
+    // copy t of slice kt (weights first) into ring slot `slot`.  Slots are counted along with the
+    // slices: a division by a ring depth that is no power of two costs more than a k-step's MFMA.
+    auto load1 = [&](int slot, int kt, int t) {
+        uint16_t* st = sm + slot * STAGE;
         const int soff = kt * BKD * 2;
-#pragma unroll
-        for (int t = 0; t < LB; ++t)
+        if (t < LB)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rW,
                 (__attribute__((address_space(3))) void*)(st + BM * BKD + (wave * LB + t) * RPI * BKD), 16,
-                (int)goffB[t], soff, 0, 0);
-#pragma unroll
-        for (int t = 0; t < LA; ++t)
+                (int)goffB[t < LB ? t : 0], soff, 0, 0);
+        else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rA,
-                (__attribute__((address_space(3))) void*)(st + (wave * LA + t) * RPI * BKD), 16,
-                (int)goffA[t], soff, 0, 0);
+                (__attribute__((address_space(3))) void*)(st + (wave * LA + t - LB) * RPI * BKD), 16,
+                (int)goffA[t < LB ? 0 : t - LB], soff, 0, 0);
     };
+    auto issue = [&](int slot, int kt) {
+#pragma unroll
+        for (int t = 0; t < L; ++t) load1(slot, kt, t);
+    };
+    auto after = [](int slot) { return slot + 1 == S ? 0 : slot + 1; };
     // persistent tiles: the tile's bias (BN floats) goes to LDS past the slabs with the DMA of its
     // first slice, so that setting the accumulators waits on no vector memory operation (a
     // global load there would also wait for the previous epilogue's stores)
@@ -364,8 +369,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
         offB[j] = BM * BKD + r * BKD;
         swB[j] = (r >> SH) & (CPR - 1);
     }
-    auto frag = [&](int kt, int ks, bf16x8 (&xa)[TI], bf16x8 (&xb)[TJ]) {
-        const uint16_t* st = sm + (kt % S) * STAGE;
+    auto frag = [&](int slot, int ks, bf16x8 (&xa)[TI], bf16x8 (&xb)[TJ]) {
+        const uint16_t* st = sm + slot * STAGE;
         const int c = ks * 2 + hl;
         // in the order the products need them (B0, A0, B1, ...)
 #pragma unroll
@@ -388,7 +393,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
     }
 #pragma unroll
     for (int p = 0; p < (AHEAD ? S : S - 1); ++p)
-        if (p < nk) issue(p);
+        if (p < nk) issue(p, p);
     issue_bias(tn);
     if (PERSIST || nk < (AHEAD ? S : S - 1)) wait_vm<0>();
     else wait_vm<(AHEAD ? S - 1 : S - 2) * L>();   // the first slice has landed
@@ -412,12 +417,15 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
     constexpr int PAIRS = NR < NM ? NR : NM;
     constexpr int PRE = NM / 4;                    // MFMAs issued before a stage barrier
     constexpr int PAIRS2 = NR < NM - PRE ? NR : NM - PRE;
+    int slot = 0;   // of the slice at hand
     auto slice = [&](int kt, auto next, auto waitn) {
+        if constexpr (S == 2) slot = kt & 1;
+        const int nslot = S == 2 ? (kt + 1) & 1 : after(slot);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const int cur = ks & 1;
             if (ks + 1 < KS) {
-                frag(kt, ks + 1, fa[cur ^ 1], fb[cur ^ 1]);
+                frag(slot, ks + 1, fa[cur ^ 1], fb[cur ^ 1]);
                 mfmas(cur, 0, NM);
 #pragma unroll
                 for (int q = 0; q < PAIRS; ++q) {
@@ -432,7 +440,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
                 __builtin_amdgcn_sched_barrier(0);
                 wait_vm<decltype(waitn)::value>();
                 bare_barrier();
-                frag(kt + 1, 0, fa[cur ^ 1], fb[cur ^ 1]);
+                frag(nslot, 0, fa[cur ^ 1], fb[cur ^ 1]);
                 mfmas(cur, PRE, NM);
 #pragma unroll
                 for (int q = 0; q < PAIRS2; ++q) {
@@ -446,10 +454,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
                 mfmas(cur, 0, NM);
             }
         }
+        slot = nslot;
     };
     using T_ = std::integral_constant<bool, true>;
     using F_ = std::integral_constant<bool, false>;
     for (;;) {   // one tile; persistent head blocks go on to tile bid + stride
+        slot = 0;
         // the accumulators start at the bias of their column (lane l, register r of MFMA tile j:
         // column (r/4)*8 + (l/32)*4 + r%4 of the tile), so the epilogue does not add it
 #pragma unroll
@@ -471,29 +481,37 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
         int kt = 0;
         if constexpr (AHEAD) {
             bf16x8 ga[2][KS][TI], gb[2][KS][TJ];
-            auto read_slice = [&](int k, bf16x8 (&xa)[KS][TI], bf16x8 (&xb)[KS][TJ]) {
+            auto read_slice = [&](int sl, bf16x8 (&xa)[KS][TI], bf16x8 (&xb)[KS][TJ]) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) frag(k, ks, xa[ks], xb[ks]);
+                for (int ks = 0; ks < KS; ++ks) frag(sl, ks, xa[ks], xb[ks]);
             };
-            auto mul_slice = [&](const bf16x8 (&xa)[KS][TI], const bf16x8 (&xb)[KS][TJ]) {
+            // the MFMAs of a slice are one chain: the copies of slice kl go between them
+            auto mul_slice = [&](const bf16x8 (&xa)[KS][TI], const bf16x8 (&xb)[KS][TJ], int kl, auto load) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
+                for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
                     for (int q = 0; q < TI * TJ; ++q) {
                         const int i = q / TJ, j = q % TJ;
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xb[ks][j], xa[ks][i],
                                                                             acc[i][j], 0, 0, 0);
                     }
+                    if constexpr (decltype(load)::value) {
+#pragma unroll
+                        for (int t = ks; t < L; t += KS) load1(slot, kl, t);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
             };
             auto step = [&](int k, auto waitn, auto load, auto par) {
                 constexpr int P = decltype(par)::value;
                 wait_vm<decltype(waitn)::value>();
                 bare_barrier();
-                if constexpr (decltype(load)::value) issue(k + S);
-                read_slice(k + 1, ga[P ^ 1], gb[P ^ 1]);
+                const int nslot = after(slot);
+                read_slice(nslot, ga[P ^ 1], gb[P ^ 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                mul_slice(ga[P], gb[P]);
+                mul_slice(ga[P], gb[P], k + S, load);   // slice k + S takes the slot of slice k
                 __builtin_amdgcn_sched_barrier(0);
+                slot = nslot;
             };
             using P0 = std::integral_constant<int, 0>; using P1 = std::integral_constant<int, 1>;
             using W = std::integral_constant<int, (S - 2) * L>;
@@ -515,12 +533,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
                     ++kt;
                 }
             });
-            if (kt & 1) mul_slice(ga[1], gb[1]);
-            else mul_slice(ga[0], gb[0]);
+            if (kt & 1) mul_slice(ga[1], gb[1], 0, F_());
+            else mul_slice(ga[0], gb[0], 0, F_());
         } else {
             frag(0, 0, fa[0], fb[0]);
             for (; kt + S - 1 < nk; ++kt) {   // steady state: a new slice enters the ring every step
-                issue(kt + S - 1);            // slot of slice kt-1: every wave read it before a barrier
+                // into the slot of slice kt-1: every wave read it before a barrier
+                issue(S == 2 ? (kt + 1) & 1 : slot == 0 ? S - 1 : slot - 1, kt + S - 1);
                 slice(kt, T_(), std::integral_constant<int, (S - 2) * L>());
             }
             drain<S - 2>([&](auto r) {        // slices kt + 1 .. nk - 1 are in flight
@@ -540,7 +559,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
         int ntm = 0, ntn = 0;
         if (more) {
             setup(nbid, ntm, ntn);
-            issue(0);
+            issue(0, 0);
             issue_bias(ntn);
         }
         if constexpr (!AHEAD) slice(kt, F_(), std::integral_constant<int, 0>());   // last slice
@@ -557,7 +576,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
             bare_barrier();   // every wave is done with its slab
             bid = nbid;
             setup(bid, tm, tn);
-            issue(0);
+            issue(0, 0);
             issue_bias(tn);
             wait_vm<0>();
             bare_barrier();
