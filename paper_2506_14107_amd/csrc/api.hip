@@ -114,6 +114,7 @@ void* scratch_base(int dev) {
     return (dev >= 0 && dev < MAX_DEVICES) ? g_scratch[dev] : nullptr;
 }
 
+constexpr int TOUCH_ROWS = 8192;   // tokens of a batch small enough to touch weights ahead
 constexpr int ROW_PAD = 256;  // GEMM operand rows are padded to a multiple of the tallest tile
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
@@ -309,6 +310,7 @@ struct dv_handle {
     void* wmem = nullptr;   // weights
     void* ws = nullptr;     // workspace
     size_t ws_bytes = 0;
+    size_t wbytes = 0;      // weights, bytes
     // weights
     const void* W_pe;
     const float *b_pe, *cls, *pos, *lnf_g, *lnf_b;
@@ -447,6 +449,15 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
     // reordered without restoration: reused rows are aliases, resolved through the root map
     const bool alias = reord && !restore;
 
+    // Small batches of a model whose weights outgrow the 256 MB of on-die cache: every layer's weights
+    // come from HBM at every call, and the row kernels ahead of the GEMMs touch them.  Measured
+    // (ViT-L/14, 24 layers): cold weights cost a layer's GEMMs about 13 us of 59 at 340 rows; 4-frame
+    // stream calls 4.06 -> 3.65 ms, batches of 16 frames 4.88 -> 4.62.  Models that stay on the die
+    // lose 2 to 9 % by it (four layers of width 1280, 26 frames: 0.86 -> 0.89 ms).
+    const bool small = T <= TOUCH_ROWS && h->wbytes > (256u << 20);
+    auto lines = [&](size_t elems) { return (uint32_t)(elems * el / 128); };
+    const size_t DD = (size_t)D * D, DM = (size_t)D * d.Dm;
+
     for (int l = 0; l < L; ++l) {
         const LayerW& w = h->layers[l];
         uint8_t* cur = wk.mask[l & 1];
@@ -486,6 +497,7 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
             ga.root = (alias && l > 0) ? wk.root : nullptr;
             ga.skip = skip;
             ga.cus = h->cus;
+            if (small) ga.touch = Touch{{w.W_qkv, w.W_o}, {lines(3 * DD), lines(DD)}, 2};
             launch_gate(bf, ga, s);
         }
         if (!dense) {
@@ -572,7 +584,9 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
         }
         {
             Scope sc(h, DV_STAGE_LN2, s);
-            launch_ln_rows(bf, wk.Z, nullptr, Mdev, T, D, w.ln2_g, w.ln2_b, wk.A, s);
+            Touch t{};
+            if (small) t = Touch{{w.W_1, w.W_2}, {lines(DM), lines(DM)}, 2};
+            launch_ln_rows(bf, wk.Z, nullptr, Mdev, T, D, w.ln2_g, w.ln2_b, wk.A, t, s);
         }
         {
             Scope sc(h, DV_STAGE_FC1, s);
@@ -1025,6 +1039,7 @@ int dv_create(const dv_config* cfg, const float* weights, size_t weights_bytes, 
         e = hipMemcpy(h->wmem, host.data(), wbytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return cleanup(fail(DV_EHIP, "weight upload: %s", hipGetErrorString(e)));
     }
+    h->wbytes = wbytes;
     char* wb = (char*)h->wmem;
     h->W_pe = wb + o_pe;
     h->b_pe = (const float*)(wb + o_bpe);

@@ -151,6 +151,15 @@ bool attention_supported(bool bf16, int N, int dh);
 void launch_im2col(bool bf16, const float* frames, int F, int S, int p, int Kp, void* A, float* x,
                    const float* cls, const float* pos, int D, int cus, hipStream_t s);
 
+// Weight matrices that launches soon after read, touched once by wavefronts of a row kernel that have
+// nothing else to do (every 128-byte line once, 4 bytes of it), so that small GEMMs, bound by the
+// latency of their loads, find them on the die instead of in HBM.  n = 0: nothing to touch.
+struct Touch {
+    const void* p[2];
+    uint32_t lines[2];   // 128-byte lines
+    int n;
+};
+
 enum GateMode : int { GATE_COS = 0, GATE_INJECT = 1, GATE_ALL = 2, GATE_NONE = 3 };
 struct GateArgs {
     float* x;             // [F*N, D] (written only to give a recomputed alias its row)
@@ -181,6 +190,7 @@ struct GateArgs {
                           // reordering; its rows already in x), the others gaps; none is gated,
                           // and inj / out_masks start at frame skip
     int cus;              // compute units of the device (0: unknown)
+    Touch touch;          // small batches only (a wavefront per token)
 };
 // Reordering with restoration: a reused row is built along its chain of sources; a group of G
 // frames has chains of at most G/4 + 1 reused links (B_dist1, B_dist2, then the P frames back
@@ -223,7 +233,8 @@ void launch_copy_rows(const float* x, const int* root, int f, int N, int D, floa
 
 // LayerNorm of rows (optionally gathered through idx) into elem rows: dst[r] = LN(src[g(r)])
 void launch_ln_rows(bool bf16, const float* src, const int* gather, const int* Mdev, int Mmax,
-                    int D, const float* g, const float* b, void* dst, hipStream_t s);
+                    int D, const float* g, const float* b, void* dst, const Touch& touch,
+                    hipStream_t s);
 // x[f*N+i] = x[r*N+i] for every token with cur[f*N+i] != 0, r = root[f*N+i] (root == nullptr:
 // the group's first frame)
 void launch_merge(float* x, const uint8_t* cur, const int* root, int F, int N, int D, int G,

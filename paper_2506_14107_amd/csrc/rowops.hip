@@ -38,6 +38,19 @@ __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const void* p, uint32_t bytes)
 }
 constexpr uint32_t ROW_SKIP = 0xFFFFFFF0u;   // an offset past every row buffer (all < 2^32 bytes)
 
+// Touch a launch's share of the weights: wavefront w of n, one instruction per 64 lines, into 256 bytes
+// of LDS that nobody reads (`sink`, the wavefront's own).
+__device__ inline void touch_lines(const Touch& t, int w, int n, float* sink) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    for (int m = 0; m < t.n; ++m) {
+        const auto r = row_rsrc(t.p[m], t.lines[m] * 128u);
+        for (uint32_t i = (uint32_t)w * WAVE + lane; i < t.lines[m]; i += (uint32_t)n * WAVE)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                r, (__attribute__((address_space(3))) void*)sink, 4, (int)(i * 128u), 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): LDS is given up with every copy landed
+}
+
 // class-token rows x[f, 0, :] = cls + pos[0] of F frames, by threads t of n
 __device__ inline void cls_rows(float* x, const float* cls, const float* pos, int F, int N, int D,
                                 size_t t, size_t n) {
@@ -164,6 +177,15 @@ template <bool BF, bool DEC, bool REORD, int CK, int NW>
 __global__ __launch_bounds__(NW * 64) void gate_k(GateArgs a) {
     const int N = a.N, D = a.D;
     const int chunks = (N + GATE_TOK - 1) / GATE_TOK;
+    if constexpr (NW == GATE_TOK) {
+        __shared__ float sink[NW][WAVE];
+        const int own = a.F * chunks;   // the blocks past the tokens' touch the coming weights
+        if ((int)blockIdx.x >= own) {
+            const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+            touch_lines(a.touch, ((int)blockIdx.x - own) * NW + w, ((int)gridDim.x - own) * NW, sink[w]);
+            return;
+        }
+    }
     const int f = blockIdx.x / chunks, ch = blockIdx.x % chunks;
     if (f < a.skip) {   // carried over from an earlier call: nothing to decide, no rows
         for (int i = ch * GATE_TOK + (int)threadIdx.x; i < min(N, (ch + 1) * GATE_TOK);
@@ -703,7 +725,8 @@ __global__ __launch_bounds__(256) void ln_rows_k(const float* __restrict__ src,
                                                  const int* __restrict__ gather,
                                                  const int* __restrict__ Mdev, int Mmax, int D,
                                                  const float* __restrict__ g,
-                                                 const float* __restrict__ b, void* dst) {
+                                                 const float* __restrict__ b, void* dst,
+                                                 Touch touch) {
     const int M = Mdev ? *Mdev : Mmax;
     const int lane = threadIdx.x & 63;
     const int nchunk = D / 4;
@@ -755,6 +778,13 @@ __global__ __launch_bounds__(256) void ln_rows_k(const float* __restrict__ src,
                 }
             }
         }
+    }
+    if (touch.n > 0) {   // wavefronts without a row; with few of them, all, after their rows
+        __shared__ float sink[4][64];
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int id = (int)blockIdx.x * 4 + w, n = (int)gridDim.x * 4;
+        const int first = n - M >= 256 ? M : 0;
+        if (id >= first) touch_lines(touch, id - first, n - first, sink[w]);
     }
 }
 
@@ -981,8 +1011,11 @@ void launch_gate(bool bf16, const GateArgs& a, hipStream_t s) {
     // one token's latency instead of four's (ViT-L/14, us a layer: 16 frames 9.4 -> 7.5, 4 frames
     // 7.2 -> 5.3)
     if (a.cus > 0 && blocks <= 2 * a.cus && a.D <= 1280) {
-        if (a.D <= 1024) launch_gate_ck<4, GATE_TOK>(v, dim3(blocks), a, s);
-        else launch_gate_ck<5, GATE_TOK>(v, dim3(blocks), a, s);
+        uint32_t lines = 0;
+        for (int m = 0; m < a.touch.n; ++m) lines = lines > a.touch.lines[m] ? lines : a.touch.lines[m];
+        const int extra = (int)((lines + GATE_TOK * 64 - 1) / (GATE_TOK * 64));   // an instruction per wavefront
+        if (a.D <= 1024) launch_gate_ck<4, GATE_TOK>(v, dim3(blocks + extra), a, s);
+        else launch_gate_ck<5, GATE_TOK>(v, dim3(blocks + extra), a, s);
     } else if (a.D <= 1024) {
         launch_gate_ck<4, 4>(v, dim3(blocks), a, s);
     } else if (a.D <= 1280) {
@@ -1034,12 +1067,13 @@ void launch_copy_rows(const float* x, const int* root, int f, int N, int D, floa
 }
 
 void launch_ln_rows(bool bf16, const float* src, const int* gather, const int* Mdev, int Mmax,
-                    int D, const float* g, const float* b, void* dst, hipStream_t s) {
+                    int D, const float* g, const float* b, void* dst, const Touch& touch,
+                    hipStream_t s) {
     const int grid = grid_for((size_t)Mmax, 4, 65536);
     // rows of at most 1024 values: 4 float4 chunks per lane in registers, else up to 8
     auto k = bf16 ? (D <= 1024 ? ln_rows_k<true, 4> : D <= 1280 ? ln_rows_k<true, 5> : ln_rows_k<true, 8>)
                   : (D <= 1024 ? ln_rows_k<false, 4> : D <= 1280 ? ln_rows_k<false, 5> : ln_rows_k<false, 8>);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, src, gather, Mdev, Mmax, D, g, b, dst);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, src, gather, Mdev, Mmax, D, g, b, dst, touch);
 }
 
 void launch_merge(float* x, const uint8_t* cur, const int* root, int F, int N, int D, int G,

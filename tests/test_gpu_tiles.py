@@ -113,3 +113,24 @@ def test_patch_gather_routes_bitwise(S, p, n, shift):
     assert np.array_equal(host(got[2]), host(one[2]))
     ref = oracle.dense_vit(host(fr)[-1:], blob, m.as_dict(), return_tokens=True)
     check_close(host(got[2])[-1:], ref[1], "bf16", "tokens")
+
+
+@pytest.mark.parametrize("reuse", [False, True])
+def test_weights_touched_ahead_bitwise(reuse):
+    """277 MB of weights: batches of up to 8192 tokens touch them ahead of the GEMMs (one frame: more
+    wavefronts without a row than with one; 28 frames), 8500 tokens do not.  The same bits."""
+    torch = require_gpu()
+    m = ModelConfig(64, 16, 11, 1024, 16, 4096, "bf16")
+    blob = synth.make_blob(m, 59)
+    n = 500
+    rng = np.random.default_rng(60)
+    base = rng.standard_normal((n // 4, 3, 64, 64))
+    fr = dev((np.repeat(base, 4, 0) + 0.3 * rng.standard_normal((n, 3, 64, 64))).astype(np.float32))
+    tau = 0.9 if reuse else float("-inf")
+    want = encoder(m, blob, n).encode(fr, 4, tau, want_tokens=True)
+    few = encoder(m, blob, 28).encode(fr[:196], 4, tau, want_tokens=True)
+    one = encoder(m, blob, 4).encode(fr[:8], 4, tau, want_tokens=True)
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert np.array_equal(host(want[k])[:196], host(few[k])), k
+        assert np.array_equal(host(want[k])[:8], host(one[k])), k
