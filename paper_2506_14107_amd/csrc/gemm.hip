@@ -307,7 +307,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
             const int r = (wave * LA + t) * RPI + lrow;
             const int c = lslot ^ ((r >> SH) & (CPR - 1));
             const int grow = m0 + tm_ * BM + r;
-            const int arow = a.a_idx ? (grow < M ? a.a_idx[grow] : 0) : grow;   // gathered A rows
+            const int live = grow < M ? grow : M - 1;   // rows past M repeat the last one
+            const int arow = a.a_idx ? a.a_idx[live] : live;   // gathered A rows
             goffA[t] = ((uint32_t)arow * K + c * 8) * 2;
         }
 #pragma unroll
@@ -640,6 +641,9 @@ void gemm_bf16_pipe_k(GemmArgs a) {
         }
     }
     switch (p.tail) {
+        case TAIL_192x256:
+            if constexpr (BN == 256) walk_tiles<E, 192, 256, 2, 2, 4, false>(a, sm, p.head, M, wave);
+            break;
         case TAIL_128x256:
             if constexpr (BN == 256) walk_tiles<E, 128, 256, 3, 2, 4, false>(a, sm, p.head, M, wave);
             break;
