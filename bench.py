@@ -130,7 +130,7 @@ def measured_traffic(stage, recorded_config):
 
 STAGE_KERNEL = {"qkv": ("Epi)1",), "oproj": ("Epi)2",), "fc1": ("Epi)3",), "fc2": ("Epi)4",),
                 "patch": ("Epi)0",),
-                "attn": ("attn_unit_k", "attn_mfma_k", "attn_wave_k"), "gate": ("gate_k",),
+                "attn": ("attn_unit_k", "attn_mfma_k", "attn_stream_k"), "gate": ("gate_k",),
                 "ln2": ("ln_rows_k",), "compact": ("compact_k",)}   # name fragments per stage
 
 

@@ -87,8 +87,9 @@ __host__ __device__ inline int div_by(int n, uint32_t magic) {
 // k order in any tile, so the plan does not change results.
 // The partial round takes the shape with the least rounds x time per tile.  Times per tile,
 // relative to a 256 x 256 tile, measured at K = 1024 and 4096 alike (per-launch overhead taken off,
-// one tile per compute unit: FC2 of width 1024, us: 70 / 57 / 41 / 28 / 19.5 / 16.5 for 256 x 256,
-// 192 x 256, 128 x 256, 128 x 128, 64 x 128, 64 x 64): the smaller the tile, the more of it is the
+// one tile per compute unit: FC2 of width 1024, us: 70 / 57 / 41 / 28 / 19 / 16.5 for 256 x 256,
+// 192 x 256, 128 x 256, 128 x 128, 64 x 128, 64 x 64; the last is 13 since its copies follow its
+// reads, which changes no choice between whole rounds): the smaller the tile, the more of it is the
 // latency of its loads, barriers and epilogue.
 enum GemmTail : int {
     TAIL_NONE = 0, TAIL_192x256, TAIL_128x256, TAIL_128x128, TAIL_64x128, TAIL_64x64

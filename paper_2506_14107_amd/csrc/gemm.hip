@@ -621,8 +621,10 @@ __device__ __forceinline__ void walk_tiles(const GemmArgs& a, uint16_t* sm, int 
 // of the large tiles.  The ring depths fill LDS: a small tile is bound by the latency of its loads.
 // Measured against one workgroup per tile, the last round in 64 x 64 tiles up to a quarter of it
 // and 128 x 128 up to half (us, before -> after; widths 1024, K = 4096 for FC2): FC2 at 340 / 700 /
-// 2056 rows 26.1 -> 18.8, 27.0 -> 19.3, 54.2 -> 31.4; QKV at 700 rows 18.6 -> 12.0; out-projection at
-// 2056 19.2 -> 12.9; at 37120 rows FC2 341 -> 312, out-projection 132 -> 125, FC1 305 -> 299.
+// 2056 rows 26.1 -> 16.3, 27.0 -> 16.9, 54.2 -> 31.4; QKV at 700 rows 18.6 -> 11.0; out-projection at
+// 2056 19.2 -> 12.6; at 37120 rows FC2 341 -> 311, out-projection 132 -> 124, FC1 305 -> 291.
+// Large launches are bound by power: QKV-shaped products of K = 4096 run 1288 TFLOP/s on random
+// operands and 1484 on zeros (hipBLASLt 1309 and 1943), whatever the schedule.
 template <Epi E, int BN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_pipe_k(GemmArgs a) {
