@@ -100,9 +100,9 @@ __device__ inline void wave_lds_sync() {
 }
 
 // Buffer descriptor over `bytes` bytes at p (raw, no stride): a load or store whose 32-bit byte
-// offset falls past `bytes` is dropped by the hardware range check.  Every GEMM operand and
-// output of the bf16 path is below 2^32 bytes (rows, padding included, are checked at handle
-// creation), so offsets are plain 32-bit products and need no 64-bit address arithmetic.
+// offset falls past `bytes` is dropped by the hardware range check.  Every workspace buffer is below
+// 2^32 bytes (rows, padding included, are checked at handle creation), so offsets into it are plain
+// 32-bit products and need no 64-bit address arithmetic; weights are addressed from their tile.
 __device__ inline __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
@@ -296,10 +296,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
     const int lr = lane & 31, hl = lane >> 5;
     const int K = a.K;
 
-    // this lane's DMA chunks: 32-bit byte offsets into the A and weight buffers (both below 2^32
-    // bytes); the k-slice advance rides in the scalar offset of buffer_load ... lds
+    // this lane's DMA chunks: 32-bit byte offsets into the A buffer (below 2^32 bytes) and the tile's
+    // own weight rows (a weight matrix may be larger); the k-slice advance rides in the scalar
+    // offset of buffer_load ... lds
     const int lrow = lane / CPR, lslot = lane % CPR;
     uint32_t goffA[LA], goffB[LB];
+    __amdgpu_buffer_rsrc_t rW;
     auto setup = [&](int b, int& tm_, int& tn_) {
         tile_coords(b, mt, tilesN, tm_, tn_);
 #pragma unroll
@@ -315,12 +317,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, uint16_t* sm, int b
         for (int t = 0; t < LB; ++t) {
             const int r = (wave * LB + t) * RPI + lrow;
             const int c = lslot ^ ((r >> SH) & (CPR - 1));
-            goffB[t] = ((uint32_t)(tn_ * BN + r) * K + c * 8) * 2;
+            goffB[t] = ((uint32_t)r * K + c * 8) * 2;
         }
+        rW = buf_rsrc((const char*)a.W + (uint64_t)(uint32_t)(tn_ * BN) * (uint32_t)(K * 2), BUF_ANY);
     };
     setup(bid, tm, tn);
     const auto rA = buf_rsrc(a.A, BUF_ANY);
-    const auto rW = buf_rsrc(a.W, BUF_ANY);
     const auto rBias = buf_rsrc(a.bias, BUF_ANY);
     // copy t of slice kt (weights first) into ring slot `slot`.  Slots are counted along with the
     // slices: a division by a ring depth that is no power of two costs more than a k-step's MFMA.
@@ -706,10 +708,10 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, float* sm, int t, in
         const int grow = tm * BT + r;
         const int arow = a.a_idx ? (grow < M ? a.a_idx[grow] : 0) : grow;   // gathered A rows
         goffA[u] = ((uint32_t)arow * K + c * 4) * 4;
-        goffB[u] = ((uint32_t)(tn * BT + r) * K + c * 4) * 4;
+        goffB[u] = ((uint32_t)r * K + c * 4) * 4;
     }
     const auto rA = buf_rsrc(a.A, BUF_ANY);
-    const auto rW = buf_rsrc(a.W, BUF_ANY);
+    const auto rW = buf_rsrc((const char*)a.W + (uint64_t)(uint32_t)(tn * BT) * (uint32_t)(K * 4), BUF_ANY);
     f32x4 acc[4][W][W];   // a chain per t: independent MFMAs, and shorter sums to round
     f32x4 bias[W];
 #pragma unroll

@@ -1,4 +1,6 @@
 """The bf16 GEMM's tile plan: every tile shape gives the same bits, at the edges of each shape."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -134,3 +136,37 @@ def test_weights_touched_ahead_bitwise(reuse):
     for k in range(3):
         assert np.array_equal(host(want[k])[:196], host(few[k])), k
         assert np.array_equal(host(want[k])[:8], host(one[k])), k
+
+
+@pytest.mark.parametrize("dtype,mlp", [("f32", (1 << 19) + 128), ("bf16", (1 << 20) + 128)])
+def test_weight_matrices_past_4_gib(dtype, mlp):
+    """W_1 [mlp, 2048] and W_2 [2048, mlp] of 2^32 + 2^20 bytes, zero but for the first and the last
+    64 hidden units (on both sides of the 4 GiB line of W_1): the bits of the model that has these
+    128 units alone, since the others add exact zeros and leave every sum's order as it is."""
+    torch = require_gpu()
+    small = ModelConfig(32, 16, 1, 2048, 16, 128, dtype)
+    w = synth.weights.make_weights(small, 61, perturb_ln=True)
+    large = dataclasses.replace(small, mlp=mlp)
+    blob = np.zeros(synth.weights.blob_floats(large), np.float32)   # pages never written stay unmapped
+    off = 0
+    for name, shape in synth.weights.weight_layout(large):
+        v = blob[off:off + int(np.prod(shape))].reshape(shape)
+        off += v.size
+        s = w[name]
+        if name in ("l0.W_1", "l0.b_1"):
+            v[:64], v[-64:] = s[:64], s[64:]
+        elif name == "l0.W_2":
+            v[:, :64], v[:, -64:] = s[:, :64], s[:, 64:]
+        else:
+            v[...] = s
+    fr = np.random.default_rng(62).standard_normal((3, 3, 32, 32)).astype(np.float32)
+    out = []
+    for m, b in ((small, synth.weights.pack_weights(w, small)), (large, blob)):
+        enc = encoder(m, b, 3)
+        out.append(enc.encode(dev(fr), 1, float("-inf"), want_masks=False, want_tokens=True))
+        torch.cuda.synchronize()
+        enc.close()
+    assert np.array_equal(host(out[0][0]), host(out[1][0]))
+    assert np.array_equal(host(out[0][2]), host(out[1][2]))
+    ref = oracle.dense_vit(fr, synth.weights.pack_weights(w, small), small.as_dict(), return_tokens=True)
+    check_close(host(out[0][2]), ref[1], dtype, "tokens")
