@@ -126,6 +126,18 @@ __host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slot
     return p;
 }
 
+// Records of a buffer descriptor whose offsets are all valid, and an offset that no buffer holds.
+constexpr uint32_t BUF_ANY = 0xFFFFFFF0u;
+
+// Byte offset of column `col` of GEMM row `row`, stored to row `out` of an output Nout wide.  Rows past
+// M, the tail of a tile, get an offset that the store drops.  They can lie past the padding of the
+// operand rows (192-row tiles after a whole number of 256), where the product may pass 2^32 and
+// come out as that of a live row.
+__host__ __device__ inline uint32_t out_offset(int row, int out, int M, uint32_t Nout, uint32_t col,
+                                               uint32_t esz) {
+    return row < M ? ((uint32_t)out * Nout + col) * esz : BUF_ANY;
+}
+
 void launch_gemm(Epi e, bool bf16, const GemmArgs& a, hipStream_t s);
 // Measurement probe: `blocks` blocks of 256 threads run `iters` rounds of four independent bf16
 // MFMA chains; returns the FLOPs the launch performs.  sink: blocks*256 floats.

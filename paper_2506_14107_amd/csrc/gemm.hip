@@ -106,8 +106,6 @@ __device__ inline void wave_lds_sync() {
 __device__ inline __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
-constexpr uint32_t BUF_ANY = 0xFFFFFFF0u;   // records of a descriptor whose offsets are all valid
-
 // Epilogue of one wavefront's (TI*32) x (TJ*32) sub-tile, staged through a wave-private LDS
 // slab so that global traffic is row-contiguous: for each 32-row slab the accumulators (lane l
 // holds row l%32, columns (r/4)*8 + (l/32)*4 + r%4 of each 32-column tile) are written to LDS,
@@ -133,7 +131,7 @@ __device__ inline void epilogue_lds(const GemmArgs& a, f32x16 (&acc)[TI][TJ], fl
     const int c = lane % CPRW, rsub = lane / CPRW;
     const uint32_t col = col0 + c * 4;
     const uint32_t Nout = a.Nout;
-    // packed-row outputs end at row M; token-row outputs drop tail rows by their offset
+    // packed-row outputs end at row M; tail rows are dropped by their offset (out_offset)
     const auto rout = buf_rsrc(a.out, SCATTER ? BUF_ANY : (uint32_t)M * Nout * ESZ);
     const auto rres = buf_rsrc(E == Epi::Patch ? (const void*)a.pos : (const void*)a.resid, BUF_ANY);
 
@@ -154,10 +152,7 @@ __device__ inline void epilogue_lds(const GemmArgs& a, f32x16 (&acc)[TI][TJ], fl
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int row = row_of(i, q);
-            if constexpr (SCATTER)
-                oo[q] = row < M ? ((uint32_t)tr[q] * Nout + col) * ESZ : BUF_ANY;
-            else
-                oo[q] = ((uint32_t)row * Nout + col) * ESZ;
+            oo[q] = out_offset(row, SCATTER ? tr[q] : row, M, Nout, col, ESZ);
         }
         if constexpr (LOADS) {
 #pragma unroll

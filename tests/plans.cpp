@@ -1,0 +1,31 @@
+// The launch rules of the kernels (host code of their headers) under C names, for test_plans.py.
+#include "dv_internal.h"
+
+using namespace dv;
+
+static int cut(int M, int Nout, int cus, int* head) {
+    const int hbn = Nout % 256 == 0 ? 256 : 128;
+    const int tiles = (M + 63) / 64 * (Nout / 64), slots = tiles < cus ? tiles : cus;
+    const GemmPlan p = gemm_plan(M, Nout, hbn, slots, div_magic(slots), div_magic(Nout / hbn));
+    *head = p.head;
+    return p.tail;
+}
+
+extern "C" {
+
+// tail shape of the bf16 GEMM's plan; *head: rows in large tiles
+int t_gemm_plan(int M, int Nout, int cus, int* head) { return cut(M, Nout, cus, head); }
+
+// the tail rows of a plan whose packed-output offset is not past the buffer of M live rows
+long long t_stray_rows(int M, int Nout, int esz, int cus) {
+    int head;
+    const int tail = cut(M, Nout, cus, &head);
+    const int bm[] = {256, 192, 128, 128, 64, 64};
+    const int from = tail == TAIL_NONE ? 0 : head, h = bm[tail];
+    const int end = from + (M - from + h - 1) / h * h;
+    long long n = 0;
+    for (int r = M; r < end; ++r)
+        n += out_offset(r, r, M, Nout, Nout - 4, esz) < (unsigned long long)M * Nout * esz;
+    return n;
+}
+}
