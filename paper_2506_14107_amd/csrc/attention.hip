@@ -6,7 +6,7 @@
 //   streamed (attn_stream_k)   four tiles of a frame and head per block, keys through a small LDS ring
 //   per frame (attn_mfma_k)    all keys of a frame and head in LDS, its tiles over eight wavefronts
 //   per unit (attn_unit_k)     star groups: the reference's keys in LDS once for a group's frames
-// launch_bf16 says which runs when, and why.
+// attn_plan.h says which runs when, and why.
 //
 // bf16 path (MFMA 32x32x16, fp32 accumulate), every quantity kept with one query per lane:
 //   S^T = K . Q^T      A = K rows from LDS, B = the query tile (registers); lane l holds the
@@ -26,7 +26,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "dv_internal.h"
+#include "attn_plan.h"
 
 namespace dv {
 
@@ -59,34 +59,6 @@ __device__ inline float wsum(float v) {
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-
-// ---- LDS geometry of the bf16 kernel (shared by host sizing and the kernel) ------------------
-// K rows: the MFMA reads 16 bytes (one chunk) of 16 consecutive rows; V rows: the transposing
-// read ds_read_b64_tr_b16 reads 8 bytes (4 dims) of 4 consecutive keys x 4 dim-words.  Row
-// strides and XOR swizzles (in 16-byte chunks) keep both patterns on distinct banks:
-//   head dim 64:  K chunk c of row r at c ^ ((r>>1)&7),  V chunk c of row j at c ^ 2((j>>1)&3)
-//   head dim 128: K chunk c of row r at c ^ (r&15),      V chunk c of row j at c ^ 2(j&3)
-//   head dim 80/96: no swizzle; K rows padded to dh+8, V rows to 96 elements.
-struct Geo {
-    int npad, dhp, ldk, ldv, dh;
-    __host__ __device__ Geo(int N, int d) : dh(d) {
-        npad = (N + 31) / 32 * 32;
-        dhp = (d + 31) / 32 * 32;
-        ldk = (d == 64 || d == 128) ? d : d + 8;
-        ldv = (d == 64 || d == 128) ? d : 96;
-    }
-    __host__ __device__ int kofs(int r, int c) const {
-        const int x = dh == 64 ? ((r >> 1) & 7) : dh == 128 ? (r & 15) : 0;
-        return r * ldk + (c ^ x) * 8;
-    }
-    __host__ __device__ int vofs(int j, int c) const {
-        const int x = dh == 64 ? 2 * ((j >> 1) & 3) : dh == 128 ? 2 * (j & 3) : 0;
-        return j * ldv + (c ^ x) * 8;
-    }
-    __host__ __device__ size_t bytes() const {
-        return ((size_t)npad * ldk + (size_t)npad * ldv) * 2;
-    }
-};
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -489,25 +461,7 @@ void launch_stream(const AttnArgs& a, hipStream_t s) {
 // contiguous rows.  Every query tile of the unit goes to one wavefront, over all key blocks:
 // no key split and no merge.
 //
-// LDS: K and V arrays of npad reference rows (keys past N repeat key N-1) followed by up to pcap
-// rows of other frames; then one 16-bit key -> row map of npad entries per frame of the group.
-struct UnitGeo {
-    Geo g;
-    int pcap, G;
-    __host__ __device__ UnitGeo(int N, int dh, int G_, int pcap_) : g(N, dh), pcap(pcap_), G(G_) {}
-    __host__ __device__ int rows() const { return g.npad + pcap; }
-    __host__ __device__ size_t vbase() const { return (size_t)rows() * g.ldk; }   // elements
-    __host__ __device__ size_t mbase() const { return vbase() + (size_t)rows() * g.ldv; }
-    __host__ __device__ size_t bytes() const { return (mbase() + (size_t)G * g.npad) * 2; }
-};
-
-// Rows of other frames that fit in `limit` bytes of LDS next to the reference rows and maps.
-inline int unit_pcap(int N, int dh, int G, size_t limit) {
-    const UnitGeo u(N, dh, G, 0);
-    const size_t per = (size_t)(u.g.ldk + u.g.ldv) * 2;
-    return u.bytes() >= limit ? 0 : (int)std::min<size_t>((limit - u.bytes()) / per, 32767);
-}
-
+// LDS as UnitGeo lays it out.
 // LDS rows dst0 .. dst0+count-1 of K and V <- packed rows src0 + min(i, nvalid - 1), head h
 template <int DH, int NT>
 __device__ __forceinline__ void stage_rows(const Geo& g, uint16_t* Ks, uint16_t* Vs,
@@ -859,58 +813,25 @@ size_t f32_lds_bytes(int N, int dh) {
     return ((size_t)N * (dh + 1) + (size_t)N * dh + (size_t)4 * dh + (size_t)4 * N) * 4;
 }
 
-// Which kernel: the same bits from each (one arithmetic per query), so the rule is about time alone.
-//   per unit   head dim 64, star groups whose reference rows leave LDS for another frame's, and
-//              units (groups x heads, one block per compute unit) that fill their rounds to 9/10: the
-//              reference's keys are staged once per group.
-//   per frame  more frames x heads than blocks are resident, and either head dim 64 with two
-//              blocks' keys per compute unit (up to 320 keys) without reuse or in groups of at most 4,
-//              or head dim 128 (one block; 64 frames of 8 heads at 90 % 31 us a layer, streamed 34).
-//   streamed   everything else: few frames, ungrouped reuse (reordering, stream calls), head dims 80
-//              and 96 or long key rows (a frame's keys fill most of LDS, eight wavefronts a unit).
-// Measured, us a layer, streamed / per frame / per unit (bf16, ViT-L/14 unless named): 256 frames
-// in groups of 8 at 50 % reuse 143 / - / 127, 90 % 80 / 143 / 57; 192 frames (1.5 rounds of units) 113 /
-// - / 138 and 73 / - / 68; 64 frames 42 / - / 64 and 29 / - / 33; reuse off, 8 frames 15 / 16 (66 without
-// several blocks to a frame), 128 frames 121 / 105; 336 px (577 keys) 60 % 168 / 222 / -, 90 % 94 / 140;
-// ViT-H/14 (head dim 80) 53 / 62; ViT-B/16, 64 frames in groups of 4, 24.5 / 22.5 / 25.7; reordered 256
-// frames at 90 % 86 / 114 (with a streaming wavefront per tile for short frames).
 template <int DH>
 void launch_bf16(const AttnArgs& a, hipStream_t s) {
-    static int per_cu = -1;
-    const size_t lds = Geo(a.N, DH).bytes();
-    if (per_cu < 0) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
+    static bool raised = false;
+    if (!raised) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
         (void)hipFuncSetAttribute((const void*)attn_mfma_k<DH>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
         if constexpr (DH == 64)
             (void)hipFuncSetAttribute((const void*)attn_unit_k<DH>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        int v = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, (const void*)attn_mfma_k<DH>, AW * 64,
-                                                         lds) != hipSuccess)
-            v = 0;
-        per_cu = v;
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
+        raised = true;
     }
-    const int items = a.F * a.H;
-    const int units = a.G > 1 ? (a.F + a.G - 1) / a.G * a.H : 0;
-    if constexpr (DH == 64) {
-        if (a.star && a.G > 1 && a.cus > 0) {
-            const int pcap = unit_pcap(a.N, DH, a.G, 160 * 1024);
-            if (pcap >= a.N && units * 10 >= (units + a.cus - 1) / a.cus * a.cus * 9) {
-                hipLaunchKernelGGL(attn_unit_k<DH>, dim3(std::min(units, a.cus)), dim3(UW * 64),
-                                   UnitGeo(a.N, DH, a.G, pcap).bytes(), s, a, pcap);
-                return;
-            }
-        }
-    }
-    bool frame = a.cus > 0 && items > (DH == 128 ? 1 : 2) * a.cus;
-    if (DH == 64) frame = frame && 2 * lds <= 160 * 1024 && (a.G <= 1 || (a.star && a.G <= 4));
-    else frame = frame && DH == 128;
-    if (!frame) {
+    const AttnPlan p = attn_plan<DH>(a);
+    if constexpr (DH == 64)
+        if (p.route == ATTN_UNIT)
+            hipLaunchKernelGGL(attn_unit_k<DH>, dim3(p.grid), dim3(UW * 64), p.lds, s, a, p.pcap);
+    if (p.route == ATTN_FRAME)
+        hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(p.grid), dim3(AW * 64), p.lds, s, a);
+    else if (p.route == ATTN_STREAM)
         launch_stream<DH>(a, s);
-        return;
-    }
-    const int grid = per_cu > 0 ? std::min(items, a.cus * per_cu) : items;
-    hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(grid), dim3(AW * 64), lds, s, a);
 }
 
 }  // namespace
@@ -920,7 +841,7 @@ size_t attention_lds_bytes(bool bf16, int N, int dh) {
 }
 
 bool attention_supported(bool bf16, int N, int dh) {
-    if (attention_lds_bytes(bf16, N, dh) > 160 * 1024) return false;
+    if (attention_lds_bytes(bf16, N, dh) > ATTN_LDS) return false;
     if (bf16) return dh == 64 || dh == 80 || dh == 96 || dh == 128;
     return dh % 16 == 0;
 }

@@ -1,5 +1,5 @@
 // The launch rules of the kernels (host code of their headers) under C names, for test_plans.py.
-#include "dv_internal.h"
+#include "attn_plan.h"
 
 using namespace dv;
 
@@ -27,5 +27,23 @@ long long t_stray_rows(int M, int Nout, int esz, int cus) {
     for (int r = M; r < end; ++r)
         n += out_offset(r, r, M, Nout, Nout - 4, esz) < (unsigned long long)M * Nout * esz;
     return n;
+}
+
+// route of a bf16 attention launch; out: blocks, bytes of LDS, rows of other frames
+int t_attn_plan(int dh, int F, int N, int H, int G, int star, int cus, long long* out) {
+    AttnArgs a{};
+    a.F = F;
+    a.N = N;
+    a.D = H * dh;
+    a.H = H;
+    a.G = G;
+    a.star = star != 0;
+    a.cus = cus;
+    const AttnPlan p = dh == 64 ? attn_plan<64>(a) : dh == 80 ? attn_plan<80>(a)
+                     : dh == 96 ? attn_plan<96>(a) : attn_plan<128>(a);
+    out[0] = p.grid;
+    out[1] = (long long)p.lds;
+    out[2] = p.pcap;
+    return p.route;
 }
 }

@@ -32,3 +32,43 @@ def test_tail_rows_are_stored_nowhere(lib, Nout, esz):
     for cus in (CUS, 304, 255, 240, 228, 192, 128):
         for M in range(last - 255, last + 1):
             assert lib.t_stray_rows(M, Nout, esz, cus) == 0, (M, cus)
+
+
+STREAM, FRAME, UNIT = range(3)
+
+
+def attn(lib, dh, F, N, H, G=0, star=True):
+    out = (ctypes.c_longlong * 3)()
+    route = lib.t_attn_plan(dh, F, N, H, G, int(star), CUS, out)
+    return route, out[0], out[1], out[2]
+
+
+def test_attention_plan_is_of_the_launch_alone(lib):
+    """The per-frame grid follows from the launch's own sizes: two blocks per compute unit at head dim
+    64 and one at 128, also after a model of 577 tokens whose keys fill the LDS of a unit."""
+    want = attn(lib, 64, 128, 257, 16)
+    assert want[:2] == (FRAME, 2 * CUS) and 2 * want[2] <= 160 << 10
+    assert attn(lib, 64, 128, 577, 16)[0] == STREAM
+    assert attn(lib, 64, 64, 197, 12, G=4)[:2] == (FRAME, 2 * CUS)
+    assert attn(lib, 64, 128, 257, 16) == want
+    assert attn(lib, 128, 64, 257, 8, G=8)[:2] == (FRAME, CUS)
+
+
+def test_attention_routes(lib):
+    """Each route of the rule, at the sizes around its lines."""
+    assert attn(lib, 64, 256, 257, 16, G=8)[0] == UNIT          # 512 units: two whole rounds
+    assert attn(lib, 64, 192, 257, 16, G=8)[0] == STREAM        # 384: a round and a half
+    assert attn(lib, 64, 256, 257, 16, G=8, star=False)[0] == STREAM
+    assert attn(lib, 64, 16, 257, 16, G=8)[0] == STREAM
+    assert attn(lib, 64, 32, 257, 16)[0] == STREAM              # no more items than resident blocks
+    assert attn(lib, 64, 33, 257, 16)[0] == FRAME
+    assert attn(lib, 64, 64, 320, 16)[0] == FRAME               # two blocks' keys: 160 KB
+    assert attn(lib, 64, 64, 321, 16)[0] == STREAM
+    assert attn(lib, 64, 64, 257, 16, G=4, star=False)[0] == STREAM
+    assert attn(lib, 128, 32, 257, 8, G=8)[0] == STREAM
+    assert attn(lib, 128, 33, 257, 8, G=8)[0] == FRAME
+    for dh in (80, 96):
+        assert attn(lib, dh, 256, 257, 16)[0] == STREAM
+    for dh, F, N, H, G in [(64, 256, 257, 16, 8), (64, 512, 289, 16, 8), (64, 512, 17, 2, 4)]:
+        route, grid, lds, pcap = attn(lib, dh, F, N, H, G)
+        assert route == UNIT and pcap >= N and lds <= 160 << 10 and grid <= CUS
