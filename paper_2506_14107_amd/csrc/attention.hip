@@ -339,11 +339,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char*
 // covered by the others' arithmetic: bound by the softmax's VALU work (577 keys, 60 % reuse: about 108
 // us a layer for 128 frames at 1336 VALU cycles a step; 168 measured).  Two or eight wavefronts a
 // block, or registers for a fourth wavefront per SIMD, were slower or equal.
-constexpr int FW = 4;   // wavefronts of a streamed block
-
 template <int DH>
 __global__ __launch_bounds__(FW * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 3 : 2, DH == 64 ? 3 : 2)))
-void attn_stream_k(AttnArgs a, int qblocks) {
+void attn_stream_k(AttnArgs a, StreamMap map) {
     constexpr int KS = DH / 16;
     constexpr int DB = (DH + 31) / 32;
     constexpr int CH = DH / 8;                       // 16-byte chunks per row
@@ -354,14 +352,8 @@ void attn_stream_k(AttnArgs a, int qblocks) {
     const Geo g(N, DH);
     uint16_t* Ks = (uint16_t*)smem;
     uint16_t* Vs = Ks + (size_t)128 * g.ldk;
-    // a unit (a group's frames, one head) lives on one XCD, its blocks one after another, so that
-    // the XCD's L2 serves the reference rows its frames share
-    const int G = a.G > 0 ? a.G : 1;
-    const int units = (a.F + G - 1) / G * a.H;
-    const int e = blockIdx.x / 8, per = G * qblocks;
-    const int u = e / per * 8 + blockIdx.x % 8, w_in = e % per;
-    const int f = u / a.H * G + w_in / qblocks, h = u % a.H, qb = w_in % qblocks;
-    if (u >= units || f >= a.F) return;
+    int f, h, qb;
+    if (!map.item(blockIdx.x, f, h, qb)) return;
     const int q0 = a.qoff[f], q1 = a.qoff[f + 1];
     const int ntile = (q1 - q0 + 31) / 32;
     const int nb = (ntile + FW - 1) / FW;            // blocks the tiles are dealt to
@@ -446,10 +438,8 @@ void launch_stream(const AttnArgs& a, hipStream_t s) {
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         raised = true;
     }
-    const int G = a.G > 0 ? a.G : 1, qblocks = ((a.N + 31) / 32 + FW - 1) / FW;
-    const int units = (a.F + G - 1) / G * a.H;
-    hipLaunchKernelGGL(attn_stream_k<DH>, dim3((units + 7) / 8 * 8 * G * qblocks), dim3(FW * 64), lds,
-                       s, a, qblocks);
+    const StreamMap map(a.F, a.skip, a.N, a.H, a.G);
+    hipLaunchKernelGGL(attn_stream_k<DH>, dim3(map.grid), dim3(FW * 64), lds, s, a, map);
 }
 
 // ---- per-unit items ----------------------------------------------------------------------------

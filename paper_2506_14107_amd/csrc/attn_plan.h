@@ -37,8 +37,54 @@ struct Geo {
     }
 };
 
-// LDS of a per-unit block: K and V arrays of npad reference rows (keys past N repeat key N-1) followed by up to pcap
-// rows of other frames; then one 16-bit key -> row map of npad entries per frame of the group.
+// ---- blocks of the streamed kernel -------------------------------------------------------------
+// A unit (a group's frames, one head) lives on one XCD, its blocks one after another, so that the
+// XCD's L2 serves the reference rows its frames share: workgroups are dealt to the 8 XCDs round-robin.
+// The frames below `skip` have no queries and get no blocks, and neither do the places of a group that
+// the batch does not fill: an empty block still waits for its LDS (4-frame calls of a ViT-L/14 stream
+// in groups of 256, 24 layers, with blocks for whole groups: the first 1974 us, now 1872; the 64th
+// 2586, now 2312).  Where whole units would leave more blocks empty than busy (few heads, a
+// last group of a frame or two) every frame is a unit of its own.
+constexpr int FW = 4;   // wavefronts (query tiles) of a streamed block
+struct StreamMap {
+    int F, H, G, skip;
+    int g0;        // the first unit's group
+    int span;      // frames per unit, at most
+    int qblocks;   // blocks per frame and head
+    int grid;
+    StreamMap(int F_, int skip_, int N, int H_, int G_) : F(F_), H(H_), G(G_ > 0 ? G_ : 1), skip(skip_) {
+        qblocks = ((N + 31) / 32 + FW - 1) / FW;
+        deal();
+        const int busy = (F - skip) * H * qblocks;
+        if (G > 1 && (grid < 0 || grid > 2 * busy)) {
+            G = 1;
+            deal();
+        }
+    }
+    // frame, head and block of the frame of grid index b; false: nothing to do
+    __host__ __device__ bool item(int b, int& f, int& h, int& qb) const {
+        const int e = b / 8, per = span * qblocks;
+        const int u = e / per * 8 + b % 8, w = e % per;
+        const int g = g0 + u / H;
+        f = (g * G > skip ? g * G : skip) + w / qblocks;
+        h = u % H;
+        qb = w % qblocks;
+        return f < F && f < (g + 1) * G;
+    }
+
+private:
+    void deal() {
+        g0 = skip / G;
+        span = std::min(G, F - skip);
+        const long long units = (long long)((F + G - 1) / G - g0) * H;
+        const long long n = (units + 7) / 8 * 8 * span * qblocks;
+        grid = n < (1ll << 31) ? (int)n : -1;
+    }
+};
+
+// LDS of a per-unit block: K and V arrays of npad reference rows (keys past N repeat key N-1) followed
+// by up to pcap rows of other frames; then one 16-bit key -> row map of npad entries per frame of
+// the group.
 struct UnitGeo {
     Geo g;
     int pcap, G;

@@ -1,4 +1,7 @@
 // The launch rules of the kernels (host code of their headers) under C names, for test_plans.py.
+#include <map>
+#include <vector>
+
 #include "attn_plan.h"
 
 using namespace dv;
@@ -45,5 +48,25 @@ int t_attn_plan(int dh, int F, int N, int H, int G, int star, int cus, long long
     out[1] = (long long)p.lds;
     out[2] = p.pcap;
     return p.route;
+}
+
+// grid of the streamed kernel, or -1 unless its blocks take every (frame from skip on, head, block of
+// the frame) exactly once and nothing else; *together: blocks that share an XCD with their unit's first
+long long t_stream_grid(int F, int skip, int N, int H, int G, long long* together) {
+    const StreamMap m(F, skip, N, H, G);
+    std::vector<int> seen((size_t)F * H * m.qblocks, 0);
+    std::map<int, int> xcd;
+    *together = 0;
+    for (int b = 0; b < m.grid; ++b) {
+        int f, h, qb;
+        if (!m.item(b, f, h, qb)) continue;
+        if (f < skip || f >= F || h < 0 || h >= H || qb < 0 || qb >= m.qblocks) return -1;
+        if (seen[((size_t)f * H + h) * m.qblocks + qb]++) return -1;
+        const int unit = f / (G > 0 ? G : 1) * H + h;
+        *together += xcd.emplace(unit, b % 8).first->second == b % 8;
+    }
+    long long n = 0;
+    for (int s : seen) n += s;
+    return n == (long long)(F - skip) * H * m.qblocks ? m.grid : -1;
 }
 }

@@ -1,0 +1,43 @@
+"""Registers and LDS of the built kernels that the launch rules count on."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2506_14107_amd import dejavu as dj
+
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Mangled name -> metadata of every kernel in the library."""
+    dj.load()
+    d = tmp_path_factory.mktemp("lib")
+    so = shutil.copy(dj.LIB_PATH, d)
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", so], check=True,
+                   capture_output=True, cwd=d)
+    out = {}
+    for obj in glob.glob(os.path.join(str(d), "*gfx950")):
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", obj], check=True,
+                               capture_output=True, text=True).stdout
+        for k in re.split(r"\n  - (?=\.agpr)", notes)[1:]:
+            name = re.search(r"\n    \.name: +(\S+)", k).group(1)
+            out[name] = {f: int(re.search(rf"\.{f}: +(\d+)", k).group(1)) for f in
+                         ("group_segment_fixed_size", "vgpr_count", "agpr_count")}
+    return out
+
+
+def of(kernels, fragment):
+    found = [v for k, v in kernels.items() if fragment in k]
+    assert found, fragment
+    return found
+
+
+def test_layernorm_rows_take_no_lds(kernels):
+    """LN2's blocks fit beside another handle's GEMM block, which holds all LDS of its compute unit; only
+    a launch that touches weights asks for some."""
+    assert all(v["group_segment_fixed_size"] == 0 for v in of(kernels, "ln_rows_k"))

@@ -72,3 +72,34 @@ def test_attention_routes(lib):
     for dh, F, N, H, G in [(64, 256, 257, 16, 8), (64, 512, 289, 16, 8), (64, 512, 17, 2, 4)]:
         route, grid, lds, pcap = attn(lib, dh, F, N, H, G)
         assert route == UNIT and pcap >= N and lds <= 160 << 10 and grid <= CUS
+
+
+@pytest.mark.parametrize("N", [17, 257, 577])
+@pytest.mark.parametrize("H", [1, 3, 12, 16, 18])
+def test_streamed_blocks(lib, N, H):
+    """Every query tile has one block, at most twice as many blocks are dealt as have work (a few per
+    XCD more where units are few), and a group's blocks of one head share an XCD where groups are
+    kept: whole batches, the first call of a stream, calls that continue one."""
+    lib.t_stream_grid.restype = ctypes.c_longlong
+    q = ((N + 31) // 32 + 3) // 4
+    for G in (0, 1, 4, 8, 12, 64, 256):
+        for F, skip in [(1, 0), (4, 0), (5, 0), (8, 0), (13, 0), (20, 0), (131, 0), (256, 0), (5, 4),
+                        (8, 4), (12, 7), (67, 63), (252, 248), (259, 255), (260, 250)]:
+            if skip and skip >= max(G, 1):
+                continue
+            together = ctypes.c_longlong()
+            grid = lib.t_stream_grid(F, skip, N, H, G, ctypes.byref(together))
+            busy = (F - skip) * H * q
+            assert busy <= grid <= 2 * busy + 8 * q, (F, skip, G)
+            if H >= 8 and F % max(G, 1) == 0 and skip == 0:
+                assert together.value == busy, (F, skip, G)
+
+
+def test_streamed_blocks_at_scratch_limits(lib):
+    """Two-token frames, as many as 32-bit offsets allow, in one group: the launch stays in range."""
+    lib.t_stream_grid.restype = ctypes.c_longlong
+    together = ctypes.c_longlong()
+    for H, F in [(1, 5592000), (10, 559000)]:
+        for G, skip in [(F, 0), (F - 1, 0), (F, F - 1), (1, 0)]:
+            grid = lib.t_stream_grid(F, skip, 2, H, G, ctypes.byref(together))
+            assert 0 < grid * 256 < 1 << 32, (H, F, G, skip)
