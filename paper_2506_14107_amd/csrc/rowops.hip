@@ -780,11 +780,11 @@ __global__ __launch_bounds__(256) void ln_rows_k(const float* __restrict__ src,
         }
     }
     if (touch.n > 0) {   // wavefronts without a row; with few of them, all, after their rows
-        __shared__ float sink[4][64];
+        extern __shared__ float sink[];   // [4][64]
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int id = (int)blockIdx.x * 4 + w, n = (int)gridDim.x * 4;
         const int first = n - M >= 256 ? M : 0;
-        if (id >= first) touch_lines(touch, id - first, n - first, sink[w]);
+        if (id >= first) touch_lines(touch, id - first, n - first, sink + w * 64);
     }
 }
 
@@ -1073,7 +1073,10 @@ void launch_ln_rows(bool bf16, const float* src, const int* gather, const int* M
     // rows of at most 1024 values: 4 float4 chunks per lane in registers, else up to 8
     auto k = bf16 ? (D <= 1024 ? ln_rows_k<true, 4> : D <= 1280 ? ln_rows_k<true, 5> : ln_rows_k<true, 8>)
                   : (D <= 1024 ? ln_rows_k<false, 4> : D <= 1280 ? ln_rows_k<false, 5> : ln_rows_k<false, 8>);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, src, gather, Mdev, Mmax, D, g, b, dst, touch);
+    // LDS for the touched lines only where there are some: a block without any fits beside a GEMM block
+    // of another stream, which holds all LDS of its compute unit
+    const size_t lds = touch.n > 0 ? 4 * 64 * sizeof(float) : 0;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, s, src, gather, Mdev, Mmax, D, g, b, dst, touch);
 }
 
 void launch_merge(float* x, const uint8_t* cur, const int* root, int F, int N, int D, int G,
