@@ -17,6 +17,11 @@ pytestmark = pytest.mark.gpu
 WIDE = ModelConfig(112, 16, 1, 256, 4, 1024, "bf16")
 NARROW = ModelConfig(112, 16, 1, 384, 6, 1536, "bf16")
 ODD_K = ModelConfig(56, 8, 1, 256, 4, 512, "bf16")
+TILE_BATCHES = (2, 7, 21, 61, 122, 190, 328, 350, 415, 700)   # frames; test_plans.py checks that they reach
+                                                         # every tail shape
+# three k-slices and four tile columns: 700 frames are two whole rounds of large tiles, whose blocks go
+# from one tile to the next with no slice copied ahead
+ODD_K_ROUNDS = ModelConfig(56, 8, 1, 1024, 16, 1024, "bf16")
 
 
 @pytest.mark.parametrize("m", [WIDE, NARROW, ODD_K], ids=["wide", "narrow", "odd-k"])
@@ -34,7 +39,7 @@ def test_tile_plan_bitwise(m):
     one = encoder(m, blob, 1)
     want = one.encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
     torch.cuda.synchronize()
-    for k in (2, 7, 21, 61, 122, 190, 328, 350, 700):
+    for k in TILE_BATCHES:
         got = big.encode(dev(fr[:k]), 1, off, want_masks=False, want_tokens=True)
         torch.cuda.synchronize()
         for x, y in ((got[0], want[0]), (got[2], want[2])):
@@ -42,6 +47,23 @@ def test_tile_plan_bitwise(m):
     ref = oracle.dense_vit(fr[-2:], blob, m.as_dict(), return_tokens=True)
     check_close(host(got[0])[-2:], ref[0], "bf16", "embeddings")
     check_close(host(got[2])[-2:], ref[1], "bf16", "tokens")
+
+
+def test_odd_slices_over_several_rounds_bitwise():
+    """The patch GEMM of 700 frames against batches of 100, which stay below one round."""
+    torch = require_gpu()
+    m, n = ODD_K_ROUNDS, 700
+    blob = synth.make_blob(m, 63)
+    fr = np.random.default_rng(64).standard_normal((n, 3, 56, 56)).astype(np.float32)
+    off = float("-inf")
+    got = encoder(m, blob, n).encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
+    few = encoder(m, blob, 100).encode(dev(fr), 1, off, want_masks=False, want_tokens=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(got[0]), host(few[0]))
+    assert np.array_equal(host(got[2]), host(few[2]))
+    for k in (0, 349, 698):
+        ref = oracle.dense_vit(fr[k:k + 2], blob, m.as_dict(), return_tokens=True)
+        check_close(host(got[2])[k:k + 2], ref[1], "bf16", "tokens")
 
 
 # fp32: head dims 16 to 128 (one attention variant each), token counts around its 64-key steps and
@@ -94,6 +116,49 @@ def test_attention_routes_bitwise(G, n):
     for k in range(3):
         assert np.array_equal(host(want[k]), host(few[k])), k
         assert np.array_equal(host(want[k]), np.concatenate([host(p[k]) for p in parts])), k
+
+
+# image, patch, width, heads, group, frames: one to five steps of 64 keys with a ragged last one, every
+# head dim, batches on both sides of the rule's lines (test_plans.py checks the routes)
+ATTENTION = {
+    "dh64-50-unit": (112, 16, 256, 4, 8, 480), "dh64-145-unit": (192, 16, 256, 4, 8, 480),
+    "dh64-257-unit": (224, 14, 256, 4, 8, 480), "dh64-145-frame": (192, 16, 256, 4, 4, 264),
+    "dh64-257-frame": (224, 14, 256, 4, 4, 264), "dh64-577-stream": (336, 14, 256, 4, 4, 24),
+    "dh80-50-stream": (112, 16, 640, 8, 4, 24), "dh80-257-stream": (224, 14, 640, 8, 4, 24),
+    "dh96-50-stream": (112, 16, 384, 4, 4, 24), "dh96-257-stream": (224, 14, 384, 4, 8, 32),
+    "dh128-50-frame": (112, 16, 256, 2, 4, 140), "dh128-145-frame": (192, 16, 256, 2, 8, 136),
+    "dh128-257-frame": (224, 14, 256, 2, 8, 136), "dh128-257-stream": (224, 14, 256, 2, 8, 120)}
+
+
+@pytest.mark.parametrize("name", ATTENTION)
+def test_attention_steps_bitwise(name):
+    """Batches on the named route against streamed blocks (internal batches of two groups; stream calls
+    of five frames): the same bits, and the last group against the oracle on the same maps."""
+    torch = require_gpu()
+    S, p, D, H, G, n = ATTENTION[name]
+    m = ModelConfig(S, p, 2, D, H, 2 * D, "bf16")
+    blob = synth.make_blob(m, 65)
+    rng = np.random.default_rng(66)
+    fr = rng.standard_normal((n, 3, S, S)).astype(np.float32)
+    g = S // p
+    for f in range(n):   # patches of each group's first frame, a third of them with noise
+        keep = rng.random((1, g, 1, g, 1)) < 0.66
+        own, ref = (fr[k].reshape(3, g, p, g, p) for k in (f, f // G * G))
+        fr[f] = np.where(keep, ref + 0.05 * own, own).reshape(3, S, S)
+    x = dev(fr)
+    big = encoder(m, blob, n)
+    want = big.encode(x, G, 0.9, want_tokens=True)
+    few = encoder(m, blob, 2 * G).encode(x, G, 0.9, want_tokens=True)
+    parts = [big.stream_encode(x[f:f + 5], G, 0.9, want_tokens=True) for f in range(0, n, 5)]
+    torch.cuda.synchronize()
+    masks = host(want[1])
+    assert 0.2 < masks.mean() < 0.8, masks.mean()
+    for k in range(3):
+        assert np.array_equal(host(want[k]), host(few[k])), k
+        assert np.array_equal(host(want[k]), np.concatenate([host(q[k]) for q in parts])), k
+    ref = oracle.encode(fr[-G:], blob, m.as_dict(), G, masks=masks[-G:])
+    check_close(host(want[0])[-G:], ref["emb"], "bf16", "embeddings")
+    check_close(host(want[2])[-G:], ref["tokens"], "bf16", "tokens")
 
 
 @pytest.mark.parametrize("S,p,n,shift", [(224, 14, 40, 0), (112, 16, 80, 0), (112, 16, 80, 1),

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from . import test_gpu_tiles as tiles
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2506_14107_amd", "csrc")
 CUS = 256
@@ -32,6 +34,35 @@ def test_tail_rows_are_stored_nowhere(lib, Nout, esz):
     for cus in (CUS, 304, 255, 240, 228, 192, 128):
         for M in range(last - 255, last + 1):
             assert lib.t_stray_rows(M, Nout, esz, cus) == 0, (M, cus)
+
+
+def gemm(lib, M, Nout):
+    head = ctypes.c_int()
+    return lib.t_gemm_plan(M, Nout, CUS, ctypes.byref(head)), head.value
+
+
+def test_batches_of_the_tile_test_reach_every_tail(lib):
+    """What test_tile_plan_bitwise compares: every tail shape of the 256-wide plan with rows in large
+    tiles and without, and every one of the 128-wide plan's."""
+    wide, narrow = set(), set()
+    for m in (tiles.WIDE, tiles.NARROW, tiles.ODD_K):
+        for k in tiles.TILE_BATCHES:
+            for Nout in (3 * m.width, m.width, m.mlp):
+                tail, head = gemm(lib, k * m.n_tokens, Nout)
+                if Nout % 256 == 0:
+                    wide.add((tail, head > 0))
+                else:
+                    narrow.add(tail)
+    assert {t for t, h in wide if h} == set(range(6)), wide
+    assert {t for t, h in wide if not h} == {1, 2, 3, 4, 5}, wide
+    assert narrow >= {0, 3, 4, 5}, narrow
+
+
+def test_odd_slice_test_walks_several_rounds(lib):
+    m = tiles.ODD_K_ROUNDS
+    assert (3 * m.patch ** 2 + 63) // 64 % 2 == 1 and m.width % 256 == 0
+    assert gemm(lib, 700 * m.n_patches, m.width)[1] // 256 * (m.width // 256) >= 2 * CUS
+    assert gemm(lib, 100 * m.n_patches, m.width)[1] == 0
 
 
 STREAM, FRAME, UNIT = range(3)
@@ -103,3 +134,13 @@ def test_streamed_blocks_at_scratch_limits(lib):
         for G, skip in [(F, 0), (F - 1, 0), (F, F - 1), (1, 0)]:
             grid = lib.t_stream_grid(F, skip, 2, H, G, ctypes.byref(together))
             assert 0 < grid * 256 < 1 << 32, (H, F, G, skip)
+
+
+@pytest.mark.parametrize("name", tiles.ATTENTION)
+def test_routes_of_the_attention_test(lib, name):
+    S, p, D, H, G, n = tiles.ATTENTION[name]
+    N = (S // p) ** 2 + 1
+    assert attn(lib, D // H, n, N, H, G)[0] == {"stream": STREAM, "frame": FRAME, "unit": UNIT}[
+        name.split("-")[2]]
+    assert attn(lib, D // H, 2 * G, N, H, G)[0] == STREAM
+    assert attn(lib, D // H, 5 + G, N, H, G, star=False)[0] == STREAM
