@@ -81,6 +81,9 @@ __host__ __device__ inline int div_by(int n, uint32_t magic) {
     return magic ? (int)(((uint64_t)(uint32_t)n * magic) >> 32) : n;
 }
 
+// Records of a buffer descriptor whose offsets are all valid, and an offset that no buffer holds.
+constexpr uint32_t BUF_ANY = 0xFFFFFFF0u;
+
 // How the M rows of a bf16 GEMM are cut: large tiles (256 x hbn) over the rows [0, head) -- the
 // tile rows that fill whole rounds of `slots` workgroups -- and one smaller tile shape over
 // [head, M), the rows of the last, partial round.  Each output is the same dot product in the same
@@ -98,8 +101,12 @@ struct GemmPlan {
     int head;
     int tail;
 };
-__host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slots,
-                                              uint32_t div_slots, uint32_t div_tn) {
+// 192-row tiles can end past the padding of the rows to 256, which bounds 32-bit offsets, by up to 128
+// rows: they are left out where such a row's place in a packed output of `esz`-byte elements would pass 2^32
+// and come out as that of a live row.  (That test, per tile row and store instead: ViT-B/16, 64 frames,
+// 0.5 % slower.)
+__host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slots, uint32_t div_slots,
+                                              uint32_t div_tn, uint32_t esz) {
     const int tn = Nout / hbn;
     const int mt = (M + 255) / 256;
     const int mA = div_by(div_by(mt * tn, div_slots) * slots, div_tn);   // whole tile rows inside the full rounds
@@ -117,25 +124,14 @@ __host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slot
         }
     };
     if (hbn == 256) {
-        consider(TAIL_192x256, 192, 256, 79);
+        const uint32_t past = (uint32_t)(M + 191);   // the last row of a 192-row tile, at most
+        if ((uint64_t)past * ((uint32_t)Nout * esz) < BUF_ANY) consider(TAIL_192x256, 192, 256, 79);
         consider(TAIL_128x256, 128, 256, 59);
     }
     consider(TAIL_128x128, 128, 128, 39);
     consider(TAIL_64x128, 64, 128, 27);
     consider(TAIL_64x64, 64, 64, 23);
     return p;
-}
-
-// Records of a buffer descriptor whose offsets are all valid, and an offset that no buffer holds.
-constexpr uint32_t BUF_ANY = 0xFFFFFFF0u;
-
-// Byte offset of column `col` of GEMM row `row`, stored to row `out` of an output Nout wide.  Rows past
-// M, the tail of a tile, get an offset that the store drops.  They can lie past the padding of the
-// operand rows (192-row tiles after a whole number of 256), where the product may pass 2^32 and
-// come out as that of a live row.
-__host__ __device__ inline uint32_t out_offset(int row, int out, int M, uint32_t Nout, uint32_t col,
-                                               uint32_t esz) {
-    return row < M ? ((uint32_t)out * Nout + col) * esz : BUF_ANY;
 }
 
 void launch_gemm(Epi e, bool bf16, const GemmArgs& a, hipStream_t s);

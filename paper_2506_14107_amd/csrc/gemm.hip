@@ -106,6 +106,8 @@ __device__ inline void wave_lds_sync() {
 __device__ inline __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
+constexpr uint32_t out_bytes(Epi e) { return e == Epi::Qkv || e == Epi::Fc1 ? 2 : 4; }   // per element
+
 // Epilogue of one wavefront's (TI*32) x (TJ*32) sub-tile, staged through a wave-private LDS
 // slab so that global traffic is row-contiguous: for each 32-row slab the accumulators (lane l
 // holds row l%32, columns (r/4)*8 + (l/32)*4 + r%4 of each 32-column tile) are written to LDS,
@@ -126,12 +128,12 @@ __device__ inline void epilogue_lds(const GemmArgs& a, f32x16 (&acc)[TI][TJ], fl
     constexpr bool LOADS = E == Epi::OProj || E == Epi::Fc2 || E == Epi::Patch || E == Epi::Restore;
     // output rows are token rows
     constexpr bool SCATTER = E == Epi::Fc2 || E == Epi::Patch || E == Epi::Restore;
-    constexpr uint32_t ESZ = (E == Epi::Qkv || E == Epi::Fc1) ? 2 : 4;   // output element bytes
+    constexpr uint32_t ESZ = out_bytes(E);
     const int lr = lane & 31, hl = lane >> 5;
     const int c = lane % CPRW, rsub = lane / CPRW;
     const uint32_t col = col0 + c * 4;
     const uint32_t Nout = a.Nout;
-    // packed-row outputs end at row M; tail rows are dropped by their offset (out_offset)
+    // packed-row outputs end at row M; token-row outputs drop tail rows by their offset
     const auto rout = buf_rsrc(a.out, SCATTER ? BUF_ANY : (uint32_t)M * Nout * ESZ);
     const auto rres = buf_rsrc(E == Epi::Patch ? (const void*)a.pos : (const void*)a.resid, BUF_ANY);
 
@@ -152,7 +154,10 @@ __device__ inline void epilogue_lds(const GemmArgs& a, f32x16 (&acc)[TI][TJ], fl
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int row = row_of(i, q);
-            oo[q] = out_offset(row, SCATTER ? tr[q] : row, M, Nout, col, ESZ);
+            if constexpr (SCATTER)
+                oo[q] = row < M ? ((uint32_t)tr[q] * Nout + col) * ESZ : BUF_ANY;
+            else
+                oo[q] = ((uint32_t)row * Nout + col) * ESZ;   // past M: past the records (gemm_plan)
         }
         if constexpr (LOADS) {
 #pragma unroll
@@ -629,7 +634,7 @@ void gemm_bf16_pipe_k(GemmArgs a) {
     uint16_t* sm = (uint16_t*)smem;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar LDS addresses
     const int M = a.Mdev ? *a.Mdev : a.Mconst;
-    const GemmPlan p = gemm_plan(M, a.Nout, BN, gridDim.x, a.div_grid, a.div_tn);
+    const GemmPlan p = gemm_plan(M, a.Nout, BN, gridDim.x, a.div_grid, a.div_tn, out_bytes(E));
     if (p.head > 0) {
         if constexpr (BN == 256) {
             pipe_tile<E, 256, 256, 64, 2, 2, 4, true>(a, sm, blockIdx.x, 0, p.head, wave, gridDim.x);

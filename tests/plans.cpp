@@ -6,10 +6,10 @@
 
 using namespace dv;
 
-static int cut(int M, int Nout, int cus, int* head) {
+static int cut(int M, int Nout, int esz, int cus, int* head) {
     const int hbn = Nout % 256 == 0 ? 256 : 128;
     const int tiles = (M + 63) / 64 * (Nout / 64), slots = tiles < cus ? tiles : cus;
-    const GemmPlan p = gemm_plan(M, Nout, hbn, slots, div_magic(slots), div_magic(Nout / hbn));
+    const GemmPlan p = gemm_plan(M, Nout, hbn, slots, div_magic(slots), div_magic(Nout / hbn), esz);
     *head = p.head;
     return p.tail;
 }
@@ -17,18 +17,19 @@ static int cut(int M, int Nout, int cus, int* head) {
 extern "C" {
 
 // tail shape of the bf16 GEMM's plan; *head: rows in large tiles
-int t_gemm_plan(int M, int Nout, int cus, int* head) { return cut(M, Nout, cus, head); }
+int t_gemm_plan(int M, int Nout, int cus, int* head) { return cut(M, Nout, 4, cus, head); }
 
-// the tail rows of a plan whose packed-output offset is not past the buffer of M live rows
+// the tail rows of a plan whose 32-bit offset in a packed output falls on a live row
 long long t_stray_rows(int M, int Nout, int esz, int cus) {
     int head;
-    const int tail = cut(M, Nout, cus, &head);
+    const int tail = cut(M, Nout, esz, cus, &head);
     const int bm[] = {256, 192, 128, 128, 64, 64};
     const int from = tail == TAIL_NONE ? 0 : head, h = bm[tail];
     const int end = from + (M - from + h - 1) / h * h;
     long long n = 0;
     for (int r = M; r < end; ++r)
-        n += out_offset(r, r, M, Nout, Nout - 4, esz) < (unsigned long long)M * Nout * esz;
+        for (uint32_t col : {0u, (uint32_t)Nout - 4})
+            n += ((uint32_t)r * Nout + col) * esz < (unsigned long long)M * Nout * esz;
     return n;
 }
 
