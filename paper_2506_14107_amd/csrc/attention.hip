@@ -452,6 +452,7 @@ void launch_stream(const AttnArgs& a, hipStream_t s) {
 // no key split and no merge.
 //
 // LDS as UnitGeo lays it out.
+
 // LDS rows dst0 .. dst0+count-1 of K and V <- packed rows src0 + min(i, nvalid - 1), head h
 template <int DH, int NT>
 __device__ __forceinline__ void stage_rows(const Geo& g, uint16_t* Ks, uint16_t* Vs,
@@ -805,23 +806,25 @@ size_t f32_lds_bytes(int N, int dh) {
 
 template <int DH>
 void launch_bf16(const AttnArgs& a, hipStream_t s) {
-    static bool raised = false;
-    if (!raised) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
-        (void)hipFuncSetAttribute((const void*)attn_mfma_k<DH>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
-        if constexpr (DH == 64)
-            (void)hipFuncSetAttribute((const void*)attn_unit_k<DH>,
+    if constexpr (frame_blocks(DH) > 0) {
+        static bool raised = false;
+        if (!raised) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
+            (void)hipFuncSetAttribute((const void*)attn_mfma_k<DH>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
-        raised = true;
+            if constexpr (DH == 64)
+                (void)hipFuncSetAttribute((const void*)attn_unit_k<DH>,
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
+            raised = true;
+        }
     }
     const AttnPlan p = attn_plan<DH>(a);
     if constexpr (DH == 64)
         if (p.route == ATTN_UNIT)
             hipLaunchKernelGGL(attn_unit_k<DH>, dim3(p.grid), dim3(UW * 64), p.lds, s, a, p.pcap);
-    if (p.route == ATTN_FRAME)
-        hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(p.grid), dim3(AW * 64), p.lds, s, a);
-    else if (p.route == ATTN_STREAM)
-        launch_stream<DH>(a, s);
+    if constexpr (frame_blocks(DH) > 0)
+        if (p.route == ATTN_FRAME)
+            hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(p.grid), dim3(AW * 64), p.lds, s, a);
+    if (p.route == ATTN_STREAM) launch_stream<DH>(a, s);
 }
 
 }  // namespace

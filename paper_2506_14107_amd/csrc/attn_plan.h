@@ -17,10 +17,9 @@ constexpr size_t ATTN_LDS = 160 * 1024;   // LDS of a compute unit
 //   head dim 128: K chunk c of row r at c ^ (r&15),      V chunk c of row j at c ^ 2(j&3)
 //   head dim 80/96: no swizzle; K rows padded to dh+8, V rows to 96 elements.
 struct Geo {
-    int npad, dhp, ldk, ldv, dh;
+    int npad, ldk, ldv, dh;
     __host__ __device__ Geo(int N, int d) : dh(d) {
         npad = (N + 31) / 32 * 32;
-        dhp = (d + 31) / 32 * 32;
         ldk = (d == 64 || d == 128) ? d : d + 8;
         ldv = (d == 64 || d == 128) ? d : 96;
     }
@@ -126,8 +125,9 @@ struct AttnPlan {
     int pcap;      // per unit: rows of other frames
 };
 // Blocks of the per-frame kernel that a compute unit holds: its registers allow 16 wavefronts at head
-// dim 64 (two blocks of eight; the rule gives it launches whose keys fit LDS twice) and 8 at 128.
-constexpr int frame_blocks(int dh) { return dh == 64 ? 2 : 1; }
+// dim 64 (two blocks of eight; the rule gives it launches whose keys fit LDS twice) and 8 at 128.  The
+// other head dims have no per-frame kernel.
+constexpr int frame_blocks(int dh) { return dh == 64 ? 2 : dh == 128 ? 1 : 0; }
 
 template <int DH>
 AttnPlan attn_plan(const AttnArgs& a) {
@@ -139,9 +139,8 @@ AttnPlan attn_plan(const AttnArgs& a) {
         if (pcap >= a.N && units * 10 >= (units + a.cus - 1) / a.cus * a.cus * 9)
             return {ATTN_UNIT, std::min(units, a.cus), UnitGeo(a.N, DH, a.G, pcap).bytes(), pcap};
     }
-    bool frame = a.cus > 0 && items > resident;
+    bool frame = resident > 0 && items > resident;
     if (DH == 64) frame = frame && 2 * lds <= ATTN_LDS && (a.G <= 1 || (a.star && a.G <= 4));
-    else frame = frame && DH == 128;
     if (frame) return {ATTN_FRAME, resident, lds, 0};
     const Geo g(a.N, DH);
     return {ATTN_STREAM, 0, (size_t)128 * (g.ldk + g.ldv) * 2, 0};

@@ -267,8 +267,5 @@ void launch_resolve(const uint8_t* cur, const uint8_t* src, int F, int N, int G,
 // emb[f] = LN(x[f*N]) (class token)
 void launch_final_ln(const float* x, int F, int N, int D, const float* g, const float* b,
                      float* emb, hipStream_t s);
-void launch_fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s);
-// out_masks[f, layer, :] = 0 for all f (dense mode)
-void launch_zero_mask_layer(uint8_t* out_masks, int F, int L, int N, int layer, hipStream_t s);
 
 }  // namespace dv

@@ -945,21 +945,6 @@ __global__ __launch_bounds__(64) void final_ln_k(const float* x, int N, int D, c
     }
 }
 
-__global__ void fill_u8_k(uint8_t* p, size_t n, uint8_t v) {
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n;
-         t += (size_t)gridDim.x * blockDim.x)
-        p[t] = v;
-}
-
-__global__ void zero_mask_layer_k(uint8_t* om, int F, int L, int N, int layer) {
-    const size_t total = (size_t)F * N;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < total;
-         t += (size_t)gridDim.x * blockDim.x) {
-        const size_t f = t / N, i = t % N;
-        om[(f * L + layer) * N + i] = 0;
-    }
-}
-
 inline int grid_for(size_t work, int per_block, int cap = 8192) {
     size_t g = (work + per_block - 1) / per_block;
     if (g < 1) g = 1;
@@ -1095,15 +1080,6 @@ void launch_final_ln(const float* x, int F, int N, int D, const float* g, const 
                      float* emb, hipStream_t s) {
     auto k = D <= 1024 ? final_ln_k<4> : D <= 1280 ? final_ln_k<5> : final_ln_k<8>;
     hipLaunchKernelGGL(k, dim3(F), dim3(64), 0, s, x, N, D, g, b, emb);
-}
-
-void launch_fill_u8(uint8_t* p, size_t n, uint8_t v, hipStream_t s) {
-    hipLaunchKernelGGL(fill_u8_k, dim3(grid_for(n, 256)), dim3(256), 0, s, p, n, v);
-}
-
-void launch_zero_mask_layer(uint8_t* om, int F, int L, int N, int layer, hipStream_t s) {
-    hipLaunchKernelGGL(zero_mask_layer_k, dim3(grid_for((size_t)F * N, 256)), dim3(256), 0, s, om,
-                       F, L, N, layer);
 }
 
 }  // namespace dv

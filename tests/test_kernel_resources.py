@@ -41,3 +41,12 @@ def test_layernorm_rows_take_no_lds(kernels):
     """LN2's blocks fit beside another handle's GEMM block, which holds all LDS of its compute unit; only
     a launch that touches weights asks for some."""
     assert all(v["group_segment_fixed_size"] == 0 for v in of(kernels, "ln_rows_k"))
+
+
+def test_per_frame_attention_blocks_per_compute_unit(kernels):
+    """Blocks of eight wavefronts, 512 registers per SIMD lane: two blocks (four wavefronts a SIMD) at head
+    dim 64, one (two a SIMD) at 128, and no such kernel at the other head dims."""
+    assert sum("attn_mfma_k" in k for k in kernels) == 2
+    assert of(kernels, "attn_mfma_kILi64E")[0]["vgpr_count"] <= 128
+    assert 128 < of(kernels, "attn_mfma_kILi128E")[0]["vgpr_count"] <= 256
+    assert all(v["group_segment_fixed_size"] == 0 for v in of(kernels, "attn_mfma_k"))
