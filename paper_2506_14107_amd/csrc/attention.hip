@@ -432,12 +432,7 @@ template <int DH>
 void launch_stream(const AttnArgs& a, hipStream_t s) {
     const Geo g(a.N, DH);
     const size_t lds = (size_t)128 * (g.ldk + g.ldv) * 2;
-    static bool raised = false;
-    if (!raised) {
-        (void)hipFuncSetAttribute((const void*)attn_stream_k<DH>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        raised = true;
-    }
+    [[maybe_unused]] static const bool allowed = allow_lds((const void*)attn_stream_k<DH>, lds);
     const StreamMap map(a.F, a.skip, a.N, a.H, a.G);
     hipLaunchKernelGGL(attn_stream_k<DH>, dim3(map.grid), dim3(FW * 64), lds, s, a, map);
 }
@@ -676,12 +671,7 @@ __global__ __launch_bounds__(256) void attn_f32_k(AttnArgs a) {
 template <int DT>
 void launch_f32(const AttnArgs& a, hipStream_t s) {
     constexpr size_t lds = (size_t)2 * FK * (DT * 16 + 4) * sizeof(float);
-    static bool raised = false;
-    if (!raised) {
-        (void)hipFuncSetAttribute((const void*)attn_f32_k<DT>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        raised = true;
-    }
+    [[maybe_unused]] static const bool allowed = allow_lds((const void*)attn_f32_k<DT>, lds);
     hipLaunchKernelGGL(attn_f32_k<DT>, dim3(a.F, a.H, (a.N + 63) / 64), dim3(256), lds, s, a);
 }
 
@@ -806,24 +796,17 @@ size_t f32_lds_bytes(int N, int dh) {
 
 template <int DH>
 void launch_bf16(const AttnArgs& a, hipStream_t s) {
-    if constexpr (frame_blocks(DH) > 0) {
-        static bool raised = false;
-        if (!raised) {   // allow more than the default dynamic LDS (gfx950 has 160 KiB per CU)
-            (void)hipFuncSetAttribute((const void*)attn_mfma_k<DH>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
-            if constexpr (DH == 64)
-                (void)hipFuncSetAttribute((const void*)attn_unit_k<DH>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)ATTN_LDS);
-            raised = true;
-        }
-    }
     const AttnPlan p = attn_plan<DH>(a);
-    if constexpr (DH == 64)
+    if constexpr (DH == 64) {
+        [[maybe_unused]] static const bool allowed = allow_lds((const void*)attn_unit_k<DH>, ATTN_LDS);
         if (p.route == ATTN_UNIT)
             hipLaunchKernelGGL(attn_unit_k<DH>, dim3(p.grid), dim3(UW * 64), p.lds, s, a, p.pcap);
-    if constexpr (frame_blocks(DH) > 0)
+    }
+    if constexpr (frame_blocks(DH) > 0) {
+        [[maybe_unused]] static const bool allowed = allow_lds((const void*)attn_mfma_k<DH>, ATTN_LDS);
         if (p.route == ATTN_FRAME)
             hipLaunchKernelGGL(attn_mfma_k<DH>, dim3(p.grid), dim3(AW * 64), p.lds, s, a);
+    }
     if (p.route == ATTN_STREAM) launch_stream<DH>(a, s);
 }
 

@@ -6,6 +6,12 @@
 
 namespace dv {
 
+// Lets kernel `k` be launched with `bytes` of dynamic LDS.  Called to initialise a static local of its
+// launcher: once, also when several host threads launch for the first time together.
+inline bool allow_lds(const void* k, size_t bytes) {
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+}
+
 // ---- bf16 storage helpers (raw 16-bit patterns) ---------------------------------------------
 __host__ __device__ inline uint16_t f32_to_bf16(float f) {
     uint32_t u = __builtin_bit_cast(uint32_t, f);

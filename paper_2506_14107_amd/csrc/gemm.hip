@@ -660,13 +660,8 @@ void gemm_bf16_pipe_k(GemmArgs a) {
 
 template <Epi E, int BN>
 void launch_pipe(const GemmArgs& a0, hipStream_t s) {
-    static bool raised = false;
     auto k = gemm_bf16_pipe_k<E, BN>;
-    if (!raised) {
-        (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)PIPE_LDS);
-        raised = true;
-    }
+    [[maybe_unused]] static const bool allowed = allow_lds((const void*)k, PIPE_LDS);
     // one block per compute unit, or per smallest tile when there are fewer
     const int tiles = ((a0.Mmax + 63) / 64) * (a0.Nout / 64);
     const int grid = std::min(tiles, a0.cus > 0 ? a0.cus : 256);

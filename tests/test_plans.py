@@ -1,6 +1,7 @@
 """The rules that choose tiles, kernels and grids, run on the host for the shapes they decide on."""
 import ctypes
 import os
+import re
 import shutil
 import subprocess
 
@@ -144,3 +145,11 @@ def test_routes_of_the_attention_test(lib, name):
         name.split("-")[2]]
     assert attn(lib, D // H, 2 * G, N, H, G)[0] == STREAM
     assert attn(lib, D // H, 5 + G, N, H, G, star=False)[0] == STREAM
+
+
+def test_launchers_keep_no_unsynchronised_state():
+    """Local statics of the host code are constants (initialised once, whatever threads come first):
+    handles of several threads launch at the same time."""
+    mutable = re.compile(r"^[ \t]+static (?!const |constexpr |inline )\w+[ \w:*]* \w+ *(?:=|;)", re.M)
+    for name in sorted(os.listdir(CSRC)):
+        assert not mutable.findall(open(os.path.join(CSRC, name)).read()), name
