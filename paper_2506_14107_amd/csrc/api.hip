@@ -454,6 +454,11 @@ int run_batch(dv_handle* h, Work& wk, const float* frames, int F, int G, int mod
     // (ViT-L/14, 24 layers): cold weights cost a layer's GEMMs about 13 us of 59 at 340 rows; 4-frame
     // stream calls 4.06 -> 3.65 ms, batches of 16 frames 4.88 -> 4.62.  Models that stay on the die
     // lose 2 to 9 % by it (four layers of width 1280, 26 frames: 0.86 -> 0.89 ms).
+    // LN2 touches W_1 and W_2 in all of them; the gate touches W_qkv and W_o only where it has a
+    // wavefront per token (launch_gate: at most two blocks per compute unit, width up to 1280), whose
+    // short blocks leave room for others.  Past that line LN2's share alone still gains: 480 frames of
+    // 17 tokens at width 1024 5561 -> 5346 us, width 1536, 24 layers: 16 frames 3309 -> 3119, 4 frames 2570
+    // -> 2441; reuse off, width 1536 0 to 1 %.
     const bool small = T <= TOUCH_ROWS && h->wbytes > (256u << 20);
     auto lines = [&](size_t elems) { return (uint32_t)(elems * el / 128); };
     const size_t DD = (size_t)D * D, DM = (size_t)D * d.Dm;
@@ -1028,7 +1033,7 @@ int dv_create(const dv_config* cfg, const float* weights, size_t weights_bytes, 
     scratch_setup(h->device);   // dv_encode_noalloc's array on this device (errors reported there)
     if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) !=
         hipSuccess)
-        h->cus = 0;   // the GEMMs then keep one tiling for all rows
+        h->cus = 0;   // the GEMMs then plan for 256, and attention takes streamed blocks
     {
         hipError_t e = hipMalloc(&h->wmem, wbytes);
         if (e != hipSuccess) {

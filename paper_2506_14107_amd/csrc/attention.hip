@@ -336,9 +336,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int f, int h, char*
 // frame's keys and values through a two-buffer ring of 64 keys (one step of attend_tile): a step's
 // rows wait in registers while the step before is computed, then go to LDS behind one barrier.  The
 // ring is small, so several blocks share a compute unit and one's barriers and load latency are
-// covered by the others' arithmetic: bound by the softmax's VALU work (577 keys, 60 % reuse: about 108
-// us a layer for 128 frames at 1336 VALU cycles a step; 168 measured).  Two or eight wavefronts a
-// block, or registers for a fourth wavefront per SIMD, were slower or equal.
+// partly covered by the others' arithmetic.  The softmax's VALU work is the largest part (577 keys, 60 %
+// reuse: about 108 us a layer for 128 frames at 1336 VALU cycles a step, of 168 measured); the rest is
+// latency that three wavefronts per SIMD leave open.  Two or eight wavefronts a block, or registers for
+// a fourth wavefront per SIMD, were slower or equal.
 template <int DH>
 __global__ __launch_bounds__(FW * 64) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 3 : 2, DH == 64 ? 3 : 2)))
 void attn_stream_k(AttnArgs a, StreamMap map) {

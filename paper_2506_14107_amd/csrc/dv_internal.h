@@ -131,7 +131,7 @@ __host__ __device__ inline GemmPlan gemm_plan(int M, int Nout, int hbn, int slot
     };
     if (hbn == 256) {
         const uint32_t past = (uint32_t)(M + 191);   // the last row of a 192-row tile, at most
-        if ((uint64_t)past * ((uint32_t)Nout * esz) < BUF_ANY) consider(TAIL_192x256, 192, 256, 79);
+        if ((uint64_t)past * ((uint32_t)Nout * esz) < BUF_ANY) consider(TAIL_192x256, 192, 256, 81);
         consider(TAIL_128x256, 128, 256, 59);
     }
     consider(TAIL_128x128, 128, 128, 39);

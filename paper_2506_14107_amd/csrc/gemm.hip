@@ -1,7 +1,8 @@
 // Packed-row GEMMs: C[M, Nout] = A[M, K] * W[Nout, K]^T + fused epilogue.
 //
-// M (the number of packed recompute rows) lives in device memory; the grid is sized for the
-// largest possible M and blocks past the live tiles return at once.
+// M (the number of packed recompute rows) lives in device memory; a workgroup per compute unit (fp32:
+// two) walks the live tiles, fewer where the largest possible M has fewer tiles, and one without a
+// tile returns at once.
 //
 // bf16 path: MFMA v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
 //   * One workgroup of eight wavefronts per compute unit walks block tiles BM x BN; the wavefronts
@@ -625,8 +626,9 @@ __device__ __forceinline__ void walk_tiles(const GemmArgs& a, uint16_t* sm, int 
 // and 128 x 128 up to half (us, before -> after; widths 1024, K = 4096 for FC2): FC2 at 340 / 700 /
 // 2056 rows 26.1 -> 16.3, 27.0 -> 16.9, 54.2 -> 31.4; QKV at 700 rows 18.6 -> 11.0; out-projection at
 // 2056 19.2 -> 12.6; at 37120 rows FC2 341 -> 311, out-projection 132 -> 124, FC1 305 -> 291.
-// Large launches are bound by power: QKV-shaped products of K = 4096 run 1288 TFLOP/s on random
-// operands and 1484 on zeros (hipBLASLt 1309 and 1943), whatever the schedule.
+// Large launches: QKV-shaped products of K = 4096 run 1288 TFLOP/s on random operands (hipBLASLt 1309) and
+// 1484 on zeros (1943).  On random operands, where switching power lowers the clock, the kernel is
+// within 2 % of the library; on zeros its own schedule holds it, so power is not its only limit.
 template <Epi E, int BN>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bf16_pipe_k(GemmArgs a) {

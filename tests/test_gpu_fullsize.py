@@ -255,7 +255,7 @@ def test_full_size_reordered_referencing():
 @pytest.mark.parametrize("reorder", [False, True], ids=["star", "reordered"])
 def test_full_size_stream_equals_one_shot(reorder):
     """ViT-L/14 (257 tokens, head dim 64) delivered as a stream of uneven calls: bit-equal to one
-    encode over all frames, so the stream path (carried-over reference, held frames, per-tile
+    encode over all frames, so the stream path (carried-over reference, held frames, streamed
     attention) meets the bar the one-shot parity tests establish."""
     torch = require_gpu()
     w = synth.get_config("vit_l14")

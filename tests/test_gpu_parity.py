@@ -21,7 +21,7 @@ N257_BF16 = ModelConfig(224, 14, 2, 128, 2, 256, "bf16")
 N577_BF16 = ModelConfig(336, 14, 1, 128, 2, 256, "bf16")
 # head dim 80 (the ViT-H/14-class width 1280 / 16 heads)
 DH80_BF16 = ModelConfig(64, 16, 2, 640, 8, 1280, "bf16")
-# head dim 80 with two key blocks per frame (N = 50): the per-frame attention kernel
+# head dim 80 with two key blocks per frame (N = 50)
 DH80_N50 = ModelConfig(112, 16, 2, 640, 8, 1280, "bf16")
 # widths past 1024 that the row kernels hold as five float4 chunks per lane: 1152 (the last
 # chunk on half of the lanes) and 1280 (the ViT-H/14-class width)
@@ -179,10 +179,10 @@ def test_batching_and_determinism_bitwise():
 
 
 def test_batching_bitwise_past_one_round_of_narrow_tiles():
-    """Width 1152 with 257 tokens: QKV (3456 outputs), the out-projection and FC2 (1152) take the
-    256 x 128 tiling, whose blocks each run one tile.  A 32-frame batch gives them well over one
-    round of head tiles (QKV: 27 tile columns); the same frames encoded 8 at a time stay under one
-    round.  Every output must be the same bit for bit, gated and with reuse off."""
+    """Width 1152 with 257 tokens: QKV (3456 outputs), the out-projection and FC2 (1152) take
+    256 x 128 tiles for whole rounds.  A 32-frame batch gives QKV (27 tile columns) several rounds,
+    whose blocks go from tile to tile; the same frames encoded 8 at a time stay under one round.
+    Every output must be the same bit for bit, gated and with reuse off."""
     torch = require_gpu()
     m = ModelConfig(224, 14, 1, 1152, 18, 2304, "bf16")
     blob = synth.make_blob(m, 41)
@@ -342,14 +342,14 @@ def test_bf16_gate_mode_parity(m):
 
 
 # N = 577 keys in two layers: a frame's keys do not fit in LDS next to another frame's, so a
-# group's frames take the per-tile wavefronts (few query tiles) or per-frame blocks
+# group's frames take streamed attention blocks
 N577_L2 = ModelConfig(336, 14, 2, 128, 2, 256, "bf16")
 
 
 @pytest.mark.parametrize("G,n", [(8, 21), (12, 24)], ids=["G8-ragged", "G12"])
 def test_large_frame_group_gate_mode_parity(G, n):
-    """Gate mode at 577 tokens over the reuse range (frames of every tile count, so both
-    kernels), groups of 8 with a short last group and of 12."""
+    """Gate mode at 577 tokens over the reuse range (frames of every tile count), groups of 8 with a
+    short last group and of 12."""
     torch = require_gpu()
     m = N577_L2
     blob = synth.make_blob(m, 27)
