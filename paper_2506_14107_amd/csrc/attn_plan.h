@@ -37,19 +37,27 @@ struct Geo {
 };
 
 // ---- blocks of the streamed kernel -------------------------------------------------------------
-// A unit (a group's frames, one head) lives on one XCD, its blocks one after another, so that the
-// XCD's L2 serves the reference rows its frames share: workgroups are dealt to the 8 XCDs round-robin.
-// The frames below `skip` have no queries and get no blocks, and neither do the places of a group that
-// the batch does not fill: an empty block still waits for its LDS (4-frame calls of a ViT-L/14 stream
-// in groups of 256, 24 layers, with blocks for whole groups: the first 1974 us, now 1872; the 64th
-// 2586, now 2312).  Where whole units would leave more blocks empty than busy (few heads, a
-// last group of a frame or two) every frame is a unit of its own.
+// A unit (a group's frames, one head) lives on one XCD, so that the XCD's L2 serves the reference rows
+// its frames share: workgroups are dealt to the 8 XCDs round-robin.  The frames below `skip` have no
+// queries and get no blocks, and neither do the places of a group that the batch does not fill: an
+// empty block still waits for its LDS (4-frame calls of a ViT-L/14 stream in groups of 256, 24 layers,
+// with blocks for whole groups: the first 1974 us, now 1872; the 64th 2586, now 2312).  Where whole
+// units would leave more blocks empty than busy (few heads, a last group of a frame or two) every
+// frame is a unit of its own.
+// Many blocks: a unit's one after another.  Few (all resident at once): an XCD deals its blocks round its
+// 32 compute units, so those that surely have queries -- the reference frames' -- come first, then
+// the other frames' first blocks, then the rest, most of them empty under reuse: two busy ones meet on
+// a unit only when more than 32 are busy.  One unit after another / this order, us a layer at 90 % reuse:
+// ViT-L/14, 8 and 12 frames 10.1 / 7.9 and 9.4 / 8.3, at 336 px 4 frames 17.8 / 13.6; 26 heads, 3
+// frames 10.2 / 8.3 (blocks for whole groups 9.9, 10.0, 16.9 and 8.3); 16 frames, 768 blocks, 10.3 / 10.5.
 constexpr int FW = 4;   // wavefronts (query tiles) of a streamed block
 struct StreamMap {
     int F, H, G, skip;
     int g0;        // the first unit's group
     int span;      // frames per unit, at most
     int qblocks;   // blocks per frame and head
+    int per_xcd;   // units of an XCD where all blocks are resident at once, else 0
+    int lead;      // 1 where a unit's first frame is its reference, computed in full
     int grid;
     StreamMap(int F_, int skip_, int N, int H_, int G_) : F(F_), H(H_), G(G_ > 0 ? G_ : 1), skip(skip_) {
         qblocks = ((N + 31) / 32 + FW - 1) / FW;
@@ -62,22 +70,39 @@ struct StreamMap {
     }
     // frame, head and block of the frame of grid index b; false: nothing to do
     __host__ __device__ bool item(int b, int& f, int& h, int& qb) const {
-        const int e = b / 8, per = span * qblocks;
-        const int u = e / per * 8 + b % 8, w = e % per;
-        const int g = g0 + u / H;
-        f = (g * G > skip ? g * G : skip) + w / qblocks;
+        int e = b / 8, k, j = 0;   // the XCD's k-th unit, the unit's j-th frame
+        if (per_xcd > 0) {
+            k = e % per_xcd;
+            const int r = e / per_xcd - lead * qblocks;
+            if (r < 0) {
+                qb = r + qblocks;
+            } else {
+                qb = r / (span - lead);
+                j = lead + r - qb * (span - lead);
+            }
+        } else {
+            const int per = span * qblocks;
+            k = e / per;
+            e -= k * per;
+            j = e / qblocks;
+            qb = e - j * qblocks;
+        }
+        const int u = k * 8 + b % 8, g = g0 + u / H;
+        f = (g * G > skip ? g * G : skip) + j;
         h = u % H;
-        qb = w % qblocks;
         return f < F && f < (g + 1) * G;
     }
 
 private:
+    static constexpr int RESIDENT = 3 * 256;   // blocks: three to a compute unit (registers)
     void deal() {
         g0 = skip / G;
+        lead = skip % G == 0;
         span = std::min(G, F - skip);
         const long long units = (long long)((F + G - 1) / G - g0) * H;
         const long long n = (units + 7) / 8 * 8 * span * qblocks;
         grid = n < (1ll << 31) ? (int)n : -1;
+        per_xcd = n <= RESIDENT ? (int)((units + 7) / 8) : 0;
     }
 };
 
